@@ -17,6 +17,7 @@ OUT_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libibp.so")
 
 HIP_SOURCES = ["ibp_api.hip", "ibp_forward.hip", "ibp_batched.hip", "ibp_backward.hip", "ibp_screen.hip",
+               "ibp_linear.hip",
                "ibp_split.hip", "ibp_crown.hip", "ibp_probe.hip"]
 HOST_SOURCES = ["ibp_build.cpp"]
 

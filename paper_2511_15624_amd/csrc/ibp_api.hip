@@ -152,6 +152,23 @@ ibp_status scratch_address(int device, void** out) {
   return IBP_OK;
 }
 
+// Where the linear sweep takes over from the dense and screened ones (k3_lin = -1).
+// Its scan costs the same for 1 and 64 boxes and its operands are padded to 64,
+// so it needs many boxes: 2000 buses, both bounds: 256 boxes 614 against 628 us,
+// 512 945 against 1143, 1024 1.47 against 2.13 ms; 4000 buses 128 boxes 1194
+// against 1059 us, 256 1577 against 2000; 8316 buses 64 boxes 1731 against 1771,
+// 128 2.49 against 3.31 ms; 1000 buses 1024 boxes 625 against 641 us, 4096 1.91
+// against 2.31 ms.  Below kLinMinElems elements the two sweeps' bounds differ by up
+// to 1e-9 (few lines carry the sum, and their float32 units differ).
+constexpr int64_t kLinMinElems = 2500000;  // outages x lines
+constexpr int64_t kLinMinWork = 3000000000ll;  // x boxes
+constexpr int64_t kLinMinBoxes = 192, kLinMinBoxesLarge = 96, kLinLarge = 80000000;
+
+bool linear_pays(const ibp::DevNet& d, int64_t n_box) {
+  const int64_t e = (int64_t)d.K * d.L;
+  return e >= kLinMinElems && e * n_box >= kLinMinWork && n_box >= (e >= kLinLarge ? kLinMinBoxesLarge : kLinMinBoxes);
+}
+
 int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
 // Restores the caller's current device on scope exit.
@@ -230,6 +247,7 @@ ibp_status to_device(ibp_network* net, int device) {
   d.zeta_inj = h.zeta_inj;
   d.zeta_f = h.zeta_f;
   d.phi_err_max = h.phi_err_max;
+  d.fmax_c_min = *std::min_element(h.fmax_ctg.begin(), h.fmax_ctg.end());
   // float64 sums of N products of a float32 PTDF entry and a float64
   // injection: each step rounds the product (when not fused) and the sum
   d.gamma64_n = (double)(2 * h.N + 64) * ibp::kU64 * 1.01;
@@ -284,6 +302,29 @@ ibp_status to_device(ibp_network* net, int device) {
     for (int k = 0; k < h.K; ++k) lt[(size_t)h.ctg_line[k] * d.Kp + k] = std::numeric_limits<float>::quiet_NaN();
     if ((st = upload(net, lt.data(), lt.size(), &d.lodfT)) != IBP_OK) return st;
     if ((st = upload(net, amax.data(), amax.size(), &d.lam_max)) != IBP_OK) return st;
+    // digit planes of the linear sweep, made on the device from the uploaded
+    // factors; without them (no memory, or a factor they cannot hold) the
+    // dense sweep serves
+    d.lin_dig = d.lin_dga = nullptr;
+    const char* tile = std::getenv("IBP_TILE");
+    const bool wanted = (int64_t)h.K * h.L >= kLinMinElems || (h.K > 0 && tile && std::strstr(tile, "k3l=1"));
+    if (wanted && *std::max_element(amax.begin(), amax.end()) < ibp::kLinMaxFactor) {
+      void* p = nullptr;
+      const size_t bytes = ibp::lin_digit_bytes(d), all = 2 * bytes + (size_t)d.Lp * 64 * sizeof(float);
+      if (hipMalloc(&p, all) == hipSuccess) {
+        net->allocs.push_back(p);
+        net->device_bytes += all;
+        int8_t* dig = static_cast<int8_t*>(p);
+        float* smp = reinterpret_cast<float*>(dig + 2 * bytes);
+        if (ibp::launch_lin_pack(d, dig, dig + bytes, smp, nullptr) != hipSuccess)
+          return fail(IBP_E_DEVICE, "packing the outage factors failed");
+        d.lin_dig = dig;
+        d.lin_dga = dig + bytes;
+        d.lin_smp = smp;
+      } else {
+        (void)hipGetLastError();
+      }
+    }
   }
   if ((st = upload(net, h.fmax_base.data(), h.L, &d.fmax_b)) != IBP_OK) return st;
   if ((st = upload(net, h.fmax_ctg.data(), h.L, &d.fmax_c)) != IBP_OK) return st;
@@ -390,6 +431,7 @@ ibp_status to_device(ibp_network* net, int device) {
     if (const char* p = std::strstr(e, "k2by=")) t.k2_by = std::atoi(p + 5);
     if (const char* p = std::strstr(e, "k5s=")) t.k5_sparse = std::atoi(p + 4) != 0;
     if (const char* p = std::strstr(e, "k3s=")) t.k3_sparse = std::atoi(p + 4) != 0;
+    if (const char* p = std::strstr(e, "k3l=")) t.k3_lin = std::atoi(p + 4) != 0;
     if (const char* p = std::strstr(e, "scru=")) t.k3_scr = std::atoi(p + 5) != 0;
     if (ibp::tune_valid(t) && ibp::tune_batched_valid(t) && (t.chord_nb == 1 || t.chord_nb == 2 || t.chord_nb == 4)) net->tune = t;
   }
@@ -462,6 +504,37 @@ void add_screen(const ibp::DevNet& d, const ibp::Tune& tune, int64_t n_box, ibp:
   lay.fscreen = tune.k3_sparse && ibp::screen_fits(d, lay) && n_chunk <= lay.n_p3;
 }
 
+// The linear sweep's arrays, in the memory of the base-flow partials (the
+// workspace does not grow); off where they do not fit.
+void add_linear(const ibp_network* net, int64_t n_box, ibp::WsLayout& lay) {
+  const ibp::DevNet& d = net->dn;
+  if (!d.lin_dig || !net->tune.k3_sparse || net->tune.k3_lin == 0) return;
+  if (net->tune.k3_lin < 0 && !linear_pays(d, n_box)) return;
+  const size_t B = (size_t)n_box, G = (B + ibp::kLinGroup - 1) / ibp::kLinGroup;
+  size_t off = lay.part2;
+  auto take = [&](size_t bytes) {
+    const size_t o = off;
+    off = align256(off + bytes);
+    return o;
+  };
+  const int n_lb = d.Lp / ibp::kLinLines, n_kt = ibp::lin_ktiles(d.K);
+  ibp::WsLayout l = lay;
+  l.oc = take(G * d.K * ibp::kLinGroup * 2 * sizeof(float));
+  l.ow = take(G * d.Kp * sizeof(float));
+  l.nk = take(G * d.Lp * sizeof(uint64_t));
+  l.hq = take(G * (d.Lp / 4) * sizeof(uint64_t));
+  l.vu = take(G * ibp::kLinGroup * d.Lp);
+  l.vl = take(G * ibp::kLinGroup * d.Lp);
+  l.n_p3 = n_lb + 2 * n_kt + ibp::lin_pair_chunks(d.K) + ibp::lin_heavy_tiles(d.Lp) * ibp::lin_heavy_chunks(d.K);
+  l.n_pe = n_lb + n_kt;
+  l.lin_lb = n_lb;
+  l.p3 = take(B * l.n_p3 * 2 * sizeof(double));
+  l.pe = take(B * l.n_pe * 2 * sizeof(double));
+  if (off > lay.part2 + B * lay.k2_by * d.Lp * 2 * sizeof(double)) return;
+  l.lin = 1;
+  lay = l;
+}
+
 ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
   if (flags & IBP_F_AUTOTUNE) {
     // the largest layout over every tile pair (smallest tiles give most
@@ -516,6 +589,10 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
   } else {
     lay.fscreen = 0;
   }
+  // one-sided calls with a screen keep it: few of their lines are swept (8192
+  // boxes at 2000 buses: 3.3 ms for screen and sweep of the upper bounds, and the
+  // linear sweep takes 3.25)
+  if (lay.batched && !(one_sided && lay.fscreen)) add_linear(net, n_box, lay);
   if (flags & (IBP_F_CROWN | IBP_F_CROWN_REF)) {
     const ibp::DevNet& d = net->dn;
     const size_t B = (size_t)std::max<int64_t>(1, n_box);

@@ -372,6 +372,8 @@ hipError_t launch_batched_sweeps(const DevNet& net, int64_t n_box, void* ws, con
     else
       hipLaunchKernelGGL(k2b_base_flows, dim3(lay.k2_gx, groups), dim3(256), 0, s, net, ws, lay, n_box, inj);
     tm->stop(t, s);
+  } else if (net.K > 0 && lay.lin) {
+    return launch_linear_sweep(net, n_box, ws, lay, s, tm);
   } else if (net.K > 0 && lay.fscreen) {
     // the line screen, then the sweep over the marked lines only
     int t = tm->start(15, s);

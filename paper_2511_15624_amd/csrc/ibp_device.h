@@ -16,7 +16,9 @@ constexpr double kKappa0 = kU32 * (1.0 + 1.0 / 1048576.0);
 
 // Per-box scalar slots in the workspace (float64).
 enum BoxSlot : int {
-  kVmax = 0,  // float bits (low 32 bits): max over outages of (|c_c| + r_c) / (1 - H_cc)
+  kVmax = 0,  // float bits (low 32 bits): max over outages of (|c_c| + r_c) / (1 - H_cc); high 32 bits (the linear
+              // sweep): outages whose line's radius exceeds its limit
+  kWmax = 1,  // float bits (the linear sweep): max over outages of |c_c| + rho'_k, and (high 32 bits) of rho'_k
   kBoxSlots = 2
 };
 
@@ -42,6 +44,9 @@ struct DevNet {
   const float* phiT;        // [N x Lp] float32 PTDF transposed (row n = column n of Phi), zero padding
   const float* lodf;        // [K x Lp] float32 outage factors, NaN at (k, c(k)), zero padding
   const float* lodfT;       // [L x Kp] the same factors line-major (row l: every outage's factor on line l)
+  const int8_t* lin_dig;    // digit planes of the outage factors (linear sweep), nullptr: that sweep is off
+  const int8_t* lin_dga;    // digit planes of their magnitudes
+  const float* lin_smp;     // [Lp][64] magnitudes of 64 outages' factors per line
   const float* lam_max;     // [Lp] max over outages of |factor| on the line, rounded up (0 on padding lines)
   const double* fmax_b;     // [L]
   const double* fmax_c;     // [L]
@@ -62,6 +67,7 @@ struct DevNet {
   const double4* seg;       // [S] (slope a, shift b, cap U, |U| if finite else 0)
   double zeta_inj, zeta_f;
   double phi_err_max;
+  double fmax_c_min;        // smallest post-outage limit
   double gamma64_n;         // float64 accumulation bound for one PTDF row
 };
 
@@ -106,6 +112,16 @@ struct WsLayout {
   size_t sw = 0;                   // float [tiles][Kp]: per tile and outage, max over its boxes of max(|c_c| - r_c, 0)
   size_t sz = 0;                   // float [tiles][k5w_bx]: per tile and 256 outages, max |c_c| + r_c
   int k5w_bx = 0;                  // blocks of 256 outages (Kp / 256 rounded up)
+  // linear outage sweep of box-tiled calls (see ibp_linear.hip), in the memory
+  // of the base-flow partials, which are dead after the line epilogue
+  int lin = 0;                     // 1: that sweep (p3 then lies in that memory too)
+  size_t oc = 0;                   // float2 [groups][K][64]: (c_c, rho'_k) of a group's boxes
+  size_t ow = 0;                   // float [groups][Kp]: the group's max |c_c| + rho'_k
+  size_t hq = 0;                   // uint64 [groups][Lp / 4]: boxes whose flow on a line of the quad is heavy
+  size_t nk = 0;                   // uint64 [groups][Lp]: boxes of the group whose flow on the line is near a kink
+  size_t vu = 0, vl = 0;           // int8 [2 groups][Lp / 32][64][16]: sign where the base penalty is active
+  size_t pe = 0;                   // double2 [B][n_pe]: sums of absolute terms (hi, lo)
+  int n_pe = 0, lin_lb = 0;        // partials per box; line blocks
   // linear-relaxation bound (present with the CROWN flag)
   size_t ccnt = 0;                 // int2 [B][Lp]: per-line (sum s, sum |s|) over outages
   size_t cv = 0;                   // double4 [B][kc_bx][K]: per-outage (sum s Lam, sum |s Lam|, count)

@@ -117,7 +117,7 @@ __device__ __forceinline__ void box_slots_init(const DevNet& net, void* ws, cons
     lh[l] = -FLT_MAX;
     lg[l] = FLT_MAX;
   }
-  if (threadIdx.x == 0) ws_ptr<double>(ws, lay.box)[b * kBoxSlots + kVmax] = 0.0;
+  if (threadIdx.x < kBoxSlots) ws_ptr<double>(ws, lay.box)[b * kBoxSlots + threadIdx.x] = 0.0;
 }
 
 // One wave per 64 buses / 64 inputs of a box (the box-tiled path): injection
@@ -384,12 +384,13 @@ __global__ __launch_bounds__(256) void k2_base_flows(DevNet net, void* ws, WsLay
 
 __device__ __forceinline__ void objective_interval(const DevNet& net, const WsLayout& lay, int64_t b,
                                                    const double (&x)[12], double* __restrict__ f_lo,
-                                                   double* __restrict__ f_hi, double* __restrict__ terms);
+                                                   double* __restrict__ f_hi, double* __restrict__ terms,
+                                                   double pad_hi = 0.0, double pad_lo = 0.0);
 
 // Objective interval of one box from all partial sums, run by one block of T
 // threads after every partial is visible.  The first T partials of each kind
 // are loaded in one group (clamped indices, masked adds); loops take the rest.
-template <int T>
+template <int T, bool LIN>
 __device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, int64_t b,
                              double* __restrict__ f_lo, double* __restrict__ f_hi,
                              double* __restrict__ terms) {
@@ -439,7 +440,8 @@ __device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, i
   }
   // one combined block reduction of the 12 running sums
   constexpr int W = T / 64;
-  __shared__ double red[W][12];
+  constexpr int F = LIN ? 14 : 12;
+  __shared__ double red[W][F];
   double x[12];
 #pragma unroll
   for (int f = 0; f < 8; ++f) x[f] = v[kP1Sc + f];
@@ -452,9 +454,24 @@ __device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, i
   if ((tid & 63) == 0)
 #pragma unroll
     for (int f = 0; f < 12; ++f) red[tid >> 6][f] = x[f];
+  if (LIN) {
+    const double2* pe = ws_ptr<double2>(ws, lay.pe) + b * lay.n_pe;
+    double eh = 0.0, el = 0.0;
+    for (int i = tid; i < lay.n_pe; i += T) {
+      const double2 e = pe[i];
+      eh += e.x;
+      el += e.y;
+    }
+    eh = wave_sum(eh);
+    el = wave_sum(el);
+    if ((tid & 63) == 0) {
+      red[tid >> 6][12] = eh;
+      red[tid >> 6][13] = el;
+    }
+  }
   __syncthreads();
-  __shared__ double tot[12];
-  if (tid < 12) {
+  __shared__ double tot[F];
+  if (tid < F) {
     double t = 0.0;
 #pragma unroll
     for (int q = 0; q < W; ++q) t += red[q][tid];
@@ -464,7 +481,29 @@ __device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, i
   if (tid != 0) return;
 #pragma unroll
   for (int f = 0; f < 12; ++f) x[f] = tot[f];
-  objective_interval(net, lay, b, x, f_lo, f_hi, terms);
+  double pad_hi = 0.0, pad_lo = 0.0;
+  if (LIN) {
+    // what the linear sweep's float64 sums (absolute terms eh, el; their
+    // exceptions add at most twice those) and its 2^-38 factors may be off,
+    // beyond the part of the totals' float32 allowance that it does not use
+    const double gF = (double)(net.L + net.K + 4096) * kU64;
+    const float wm = __uint_as_float(
+        *reinterpret_cast<const unsigned*>(ws_ptr<double>(ws, lay.box) + b * kBoxSlots + kWmax));
+    const double q = (double)wm > 32768.0 * net.fmax_c_min ? 0x1p-38 * wm * net.L * net.K : 0.0;
+    // an overflowing flow leaves no number: the trivial bounds then
+    if (!(fabs(x[10]) < INFINITY)) x[10] = INFINITY;
+    if (!(fabs(x[11]) < INFINITY)) x[11] = 0.0;
+    x[10] = fmax(x[10], 0.0);
+    x[11] = fmax(x[11], 0.0);
+    if (x[10] < INFINITY) pad_hi = fmax(q + 4.0 * gF * tot[12] - 0.5 * kU32 * x[10], 0.0);
+    pad_lo = fmax(q + 4.0 * gF * tot[13] - 0.5 * kU32 * x[11], 0.0);
+    if (!(pad_lo < INFINITY)) x[11] = pad_lo = 0.0;
+    if (!(pad_hi < INFINITY)) pad_hi = INFINITY;
+    // a side that the call does not compute holds nothing
+    if (lay.sides == 1) pad_hi = 0.0;
+    if (lay.sides == 2) pad_lo = 0.0;
+  }
+  objective_interval(net, lay, b, x, f_lo, f_hi, terms, pad_hi, pad_lo);
 }
 
 // Objective interval of box b from its summed terms: x[0..7] the box-
@@ -473,7 +512,8 @@ __device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, i
 // the base penalties (hi, lo), x[10], x[11] the outage penalties (hi, lo).
 __device__ __forceinline__ void objective_interval(const DevNet& net, const WsLayout& lay, int64_t b,
                                                    const double (&x)[12], double* __restrict__ f_lo,
-                                                   double* __restrict__ f_hi, double* __restrict__ terms) {
+                                                   double* __restrict__ f_hi, double* __restrict__ terms,
+                                                   double pad_hi, double pad_lo) {
   double v[kP1Fields];
 #pragma unroll
   for (int f = 0; f < 8; ++f) v[kP1Sc + f] = x[f];
@@ -499,8 +539,8 @@ __device__ __forceinline__ void objective_interval(const DevNet& net, const WsLa
   // float64 accumulation depth is far below L + K + 4096 additions per term
   const double gF = (double)(net.L + net.K + 4096) * kU64;
   const double Fb_hi = bh * (1.0 + gF), Fb_lo = bl * (1.0 - gF);
-  const double Fc_hi = chs * (1.0 + 4.0 * kU32) * (1.0 + gF);
-  const double Fc_lo = cls * (1.0 - 4.0 * kU32) * (1.0 - gF);
+  const double Fc_hi = chs * (1.0 + 4.0 * kU32) * (1.0 + gF) + pad_hi;
+  const double Fc_lo = fmax(cls * (1.0 - 4.0 * kU32) * (1.0 - gF) - pad_lo, 0.0);
   const double zi = net.zeta_inj, zf = net.zeta_f;
   double hi = S_hi - zi * I_lo - zf * (Fb_lo + Fc_lo);
   hi += 8.0 * kU64 * (fabs(S_hi) + zi * I_lo + zf * (Fb_lo + Fc_lo));
@@ -524,16 +564,19 @@ __device__ __forceinline__ void objective_interval(const DevNet& net, const WsLa
 }
 
 // One block of T threads per box.
-template <int T>
+template <int T, bool LIN>
 __global__ __launch_bounds__(T) void k4_finalize(DevNet net, void* ws, WsLayout lay, int64_t box0,
                                                  double* __restrict__ f_lo, double* __restrict__ f_hi,
                                                  double* __restrict__ terms) {
-  finalize_box<T>(net, ws, lay, box0 + blockIdx.x, f_lo, f_hi, terms);
+  finalize_box<T, LIN>(net, ws, lay, box0 + blockIdx.x, f_lo, f_hi, terms);
 }
 
 static void launch_k4(const DevNet& net, void* ws, const WsLayout& lay, int64_t b0, int nb, double* f_lo,
                       double* f_hi, double* terms, hipStream_t s) {
-  hipLaunchKernelGGL(k4_finalize<256>, dim3(nb), dim3(256), 0, s, net, ws, lay, b0, f_lo, f_hi, terms);
+  if (lay.lin)
+    hipLaunchKernelGGL((k4_finalize<256, true>), dim3(nb), dim3(256), 0, s, net, ws, lay, b0, f_lo, f_hi, terms);
+  else
+    hipLaunchKernelGGL((k4_finalize<256, false>), dim3(nb), dim3(256), 0, s, net, ws, lay, b0, f_lo, f_hi, terms);
 }
 
 // ---------------------------------------------------------------- K3
@@ -863,7 +906,7 @@ hipError_t launch_forward_single(const DevNet& net, int64_t n_box, const float* 
         default: launch_k3<16>(net, ws, lay, b0, nb, s, tm); break;
       }
     }
-    tm->launch(3, k4_finalize<256>, dim3(nb), dim3(256), s, net, ws, lay, b0, f_lo, f_hi, terms);
+    tm->launch(3, k4_finalize<256, false>, dim3(nb), dim3(256), s, net, ws, lay, b0, f_lo, f_hi, terms);
   }
   return hipGetLastError();
 }

@@ -59,6 +59,7 @@ struct Tune {
   int k2_by = 0;    // bus chunks of the matrix-core base flows (0: by rule)
   int k5_sparse = 1; // box-tiled gradient of f_hi: screened sweep over candidate lines (0: dense sweep)
   int k3_sparse = 1; // box-tiled one-sided forward: screened sweep over candidate lines (0: dense sweep)
+  int k3_lin = -1;   // box-tiled forward: linear sweep 0 off, 1 wherever it fits, -1 by size (needs k3_sparse)
   int k3_scr = 0;    // box-tiled calls bounding f_lo screen the upper penalties (as IBP_F_SCREEN_UPPER)
 };
 
@@ -95,6 +96,24 @@ void launch_line_screen(const DevNet& net, int64_t n_box, void* ws, const WsLayo
 // mode; writes the outage-penalty partials that the finalize reads.
 void launch_screened_forward_sweep(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, int sides,
                                    hipStream_t s);
+// Linear outage sweep (see ibp_linear.hip): boxes per group (a lane each), lines
+// per block, digits of a factor, and the largest factor the digits hold.
+constexpr int kLinGroup = 64;
+constexpr int kLinLines = 32;
+constexpr int kLinDigits = 5;
+constexpr float kLinMaxFactor = 1.9f;
+inline int lin_ktiles(int K) { return (K + 31) / 32; }
+inline int lin_pair_chunks(int K) { return (K + 1023) / 1024; }
+constexpr int kHeavyLines = 128, kHeavyK = 512;
+inline int lin_heavy_tiles(int Lp) { return (Lp + kHeavyLines - 1) / kHeavyLines; }
+inline int lin_heavy_chunks(int K) { return (K + kHeavyK - 1) / kHeavyK; }
+inline size_t lin_digit_bytes(const DevNet& net) {
+  return (size_t)lin_ktiles(net.K) * (net.Lp / 32) * kLinDigits * 1024;
+}
+hipError_t launch_lin_pack(const DevNet& net, int8_t* dig, int8_t* dga, float* smp, hipStream_t s);
+// The outage penalties of lay.sides for every box, after the line epilogue.
+hipError_t launch_linear_sweep(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, hipStream_t s,
+                               KernelTimer* tm);
 bool tune_valid(const Tune& t);
 bool tune_batched_valid(const Tune& t);
 int batched_rows_rule(const DevNet& net, int k3_bx, int64_t groups);
