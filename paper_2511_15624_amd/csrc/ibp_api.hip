@@ -484,9 +484,9 @@ std::vector<ibp::Tune> flow_candidates(const ibp_network* net, const ibp::Tune& 
 // box-tiled layout; fscreen says whether the screened forward sweep fits it
 // (one outage-penalty partial per chunk of 64 kSparseQ outages in the
 // finalize's slots).
-void add_screen(const ibp::DevNet& d, const ibp::Tune& tune, int64_t n_box, ibp::WsLayout& lay) {
+void add_screen(const ibp::DevNet& d, const ibp::Tune& tune, int64_t n_box, ibp::WsLayout& lay, size_t at = 0) {
   const size_t B = (size_t)std::max<int64_t>(1, n_box);
-  size_t off = lay.total;
+  size_t off = at ? at : lay.total;
   auto take = [&](size_t bytes) {
     const size_t o = off;
     off = align256(off + bytes);
@@ -499,7 +499,7 @@ void add_screen(const ibp::DevNet& d, const ibp::Tune& tune, int64_t n_box, ibp:
   lay.k5w_bx = (d.Kp + 255) / 256;
   lay.sw = take(tiles * d.Kp * sizeof(float));
   lay.sz = take(tiles * lay.k5w_bx * sizeof(float));
-  lay.total = off;
+  lay.total = std::max(lay.total, off);
   const int n_chunk = (d.K + 64 * ibp::kSparseQ - 1) / (64 * ibp::kSparseQ);
   lay.fscreen = tune.k3_sparse && ibp::screen_fits(d, lay) && n_chunk <= lay.n_p3;
 }
@@ -616,6 +616,26 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
       lay.vtx = take(B * d.X * sizeof(float));
     }
     lay.total = off;
+    // the screened slopes of the upper relaxation: the screen's regions in the
+    // memory of the base-flow partials (dead by then) where they fit there
+    // (IBP_TILE=k5s=0 keeps the dense sweep).  The screen and its marks cost a few
+    // launches: 2000 buses, 8 boxes 295 against 230 us, 64 boxes 471 against 583,
+    // 1024 3.35 against 6.67 ms; 8316 buses, 4 boxes 1280 against 1234 us, 64 3.65
+    // against 5.11 ms; 500 buses, 1024 boxes the same.
+    const bool pays = net->tune.k5_sparse && (int64_t)d.K * d.L * n_box >= 500000000;
+    if (lay.batched && d.K > 0 && pays && lay.k5s_tiles) {
+      lay.rscreen = ibp::screen_fits(d, lay);
+    } else if (lay.batched && d.K > 0 && pays) {
+      ibp::WsLayout l = lay;
+      l.total = 0;
+      add_screen(d, net->tune, n_box, l, lay.part2);
+      if (l.total <= lay.part2 + B * lay.k2_by * d.Lp * 2 * sizeof(double) && ibp::screen_fits(d, l)) {
+        l.total = lay.total;
+        l.fscreen = lay.fscreen;
+        l.rscreen = 1;
+        lay = l;
+      }
+    }
   }
   return lay;
 }

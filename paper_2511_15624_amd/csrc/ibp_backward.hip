@@ -446,9 +446,18 @@ __global__ __launch_bounds__(256) void k5b_outage_vjp(DevNet net, void* ws, WsLa
 // ALUs; the line side needs two counts per box (active elements, and those
 // among them with negative flow), which the test's lane masks give by scalar
 // popcounts, added to the line's counter by one atomic per box and line.
-template <int Q>
+//
+// The lines may be walked in segments by several waves (2000 buses, 8 boxes, the
+// whole backward: 969 -> 300 us), each with its own per-outage sums.
+//
+// RELAX: the same walk for the slopes of the upper relaxation (s = sign(C) where
+// the forward's padded lower penalty is active): unit weights, and per outage the
+// sums of s Lam and |s Lam| and the count.  Their error bound allows ten float32
+// roundings, so eight lines are summed in float32 and those sums in float64
+// (16 float64 additions of each per eight lines).
+template <int Q, bool RELAX>
 __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout lay, int64_t n_box,
-                                                 const double* __restrict__ g_hi, int n_chunk, int n_tg) {
+                                                 const double* __restrict__ g_hi, int n_chunk, int n_tg, int n_seg) {
   constexpr int S = kScreenBoxes;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -456,21 +465,23 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
   // The blocks of one XCD (dispatch order: block id mod 8) take consecutive
   // units in chunk-major order, so each XCD streams one or two chunks and
   // their factor columns stay in its L2.
-  const int U = n_chunk * n_tg;
+  const int U = n_chunk * n_seg * n_tg;
   const int per = (U + 7) / 8;
   const int slot = blockIdx.x >> 3;
   const int u = (blockIdx.x & 7) * per + slot;
   if (slot >= per || u >= U) return;  // the whole block
   const int tile = (u % n_tg) * 4 + w;
   const bool on = tile < lay.k5s_tiles;
-  const int kw = (u / n_tg) * 64 * Q;
+  const int seg = (u / n_tg) % n_seg;  // of the lines (sweep_segments), a wave each
+  const int kw = (u / n_tg / n_seg) * 64 * Q;
   // the tile's candidate-line masks, staged in LDS: reading them there keeps
   // the walk free of vector-memory waits
   __shared__ uint64_t smk_all[4][kSparseMaxWords];
   uint64_t* smk = smk_all[w];
-  const int words = net.Lp / 64;
+  const int per_seg = (net.Lp / 64 + n_seg - 1) / n_seg, word0 = seg * per_seg;
+  const int words = min(per_seg, net.Lp / 64 - word0);  // of this segment (may be none)
   if (on) {
-    const uint64_t* mask = ws_ptr<uint64_t>(ws, lay.smask) + (size_t)tile * words;
+    const uint64_t* mask = ws_ptr<uint64_t>(ws, lay.smask) + (size_t)tile * (net.Lp / 64) + word0;
     for (int j = lane; j < words; j += 64) smk[j] = mask[j];
   }
   __syncthreads();
@@ -482,8 +493,18 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
 #pragma unroll
   for (int i = 0; i < S; ++i) {
     bb[i] = min(b0 + i, n_box - 1);
-    clo[i] = (float)(-net.zeta_f * g_hi[bb[i]]);
+    clo[i] = RELAX ? 0.0f : (float)(-net.zeta_f * g_hi[bb[i]]);
   }
+  double dc[RELAX ? Q : 1][S], dr[RELAX ? Q : 1][S];
+  unsigned nk[RELAX ? Q : 1][S];
+  if (RELAX)
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int i = 0; i < S; ++i) {
+        dc[RELAX ? q : 0][i] = dr[RELAX ? q : 0][i] = 0.0;
+        nk[RELAX ? q : 0][i] = 0u;
+      }
   float cc[Q][S], rc[Q][S], pc[Q][S], pr[Q][S];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
@@ -491,7 +512,13 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
     const int kq = min(k, net.K - 1);
 #pragma unroll
     for (int i = 0; i < S; ++i) {
-      const float2 v = cb[bb[i] * net.K + kq];
+      float2 v;
+      if (RELAX) {
+        const int4 d = ws_ptr<int4>(ws, lay.ctg)[bb[i] * net.K + kq];
+        v = make_float2(__int_as_float(d.y), __int_as_float(d.z));
+      } else {
+        v = cb[bb[i] * net.K + kq];
+      }
       cc[q][i] = v.x;
       rc[q][i] = k < net.K ? v.y : INFINITY;  // lanes past the last outage: never active
       pc[q][i] = pr[q][i] = 0.0f;
@@ -501,7 +528,7 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
   // write them, so their wave-uniform loads become scalar loads into SGPRs
   typedef __attribute__((address_space(4))) const float const_float;
   const_float* rec = (const_float*)(ws_ptr<float>(ws, lay.srec) + (size_t)tile * net.Lp * kScreenRecFloats);
-  unsigned long long* cnt = ws_ptr<unsigned long long>(ws, lay.lcnt);
+  unsigned long long* cnt = ws_ptr<unsigned long long>(ws, RELAX ? lay.ccnt : lay.lcnt);
   // rows are padded to whole chunks (zero factors past the last outage, whose
   // tests fail: rc = inf)
   static_assert(64 * Q <= 256, "a chunk must fit the 256-outage row padding");
@@ -528,6 +555,7 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
         const float mm = act ? x[q] : 0.0f;
         pc[q][i] += neg ? -mm : mm;
         pr[q][i] += fabsf(mm);
+        if (RELAX) nk[RELAX ? q : 0][i] += act;
         const uint64_t ba = __builtin_amdgcn_ballot_w64(act);
         na[i] += (unsigned)__builtin_popcountll(ba);
         nn[i] += (unsigned)__builtin_popcountll(ba & __builtin_amdgcn_ballot_w64(neg));
@@ -562,11 +590,21 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
              (unsigned)__builtin_amdgcn_readlane((int)(unsigned)mw, i);
       ++j;
     }
-    const int l = (j - 1) * 64 + __builtin_ctzll(bits);
+    const int l = (word0 + j - 1) * 64 + __builtin_ctzll(bits);
     bits &= bits - 1;
     return l;
   };
-  int pl = -1;
+  int pl = -1, run = 0;
+  auto flush = [&]() {
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int i = 0; i < S; ++i) {
+        dc[RELAX ? q : 0][i] += (double)pc[q][i];
+        dr[RELAX ? q : 0][i] += (double)pr[q][i];
+        pc[q][i] = pr[q][i] = 0.0f;
+      }
+  };
   float4 pc4 = make_float4(0.f, 0.f, 0.f, 0.f), pr4 = pc4;
   float px[Q];
 #pragma unroll
@@ -578,6 +616,10 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
 #pragma unroll
     for (int q = 0; q < Q; ++q) x[q] = lamT[(size_t)l * net.Kp + 64 * q];
     if (pl >= 0) line_step(pl, pc4, pr4, px);
+    if (RELAX && ++run == 8) {
+      flush();
+      run = 0;
+    }
     pl = l;
     pc4 = c4;
     pr4 = r4;
@@ -585,15 +627,33 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
     for (int q = 0; q < Q; ++q) px[q] = x[q];
   }
   if (pl >= 0) line_step(pl, pc4, pr4, px);
+  if (RELAX) flush();
   float2* cp = ws_ptr<float2>(ws, lay.cpart);
+  double4* cv = ws_ptr<double4>(ws, lay.cv);
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int k = kw + 64 * q + lane;
 #pragma unroll
     for (int i = 0; i < S; ++i)
-      if (k < net.K && b0 + i < n_box)
-        cp[(size_t)(b0 + i) * net.K + k] = make_float2(clo[i] * pc[q][i], -clo[i] * pr[q][i]);
+      if (k < net.K && b0 + i < n_box) {
+        if (RELAX)
+          cv[((size_t)(b0 + i) * n_seg + seg) * net.K + k] =
+              make_double4(dc[RELAX ? q : 0][i], dr[RELAX ? q : 0][i], (double)nk[RELAX ? q : 0][i], 0.0);
+        else
+          cp[((size_t)(b0 + i) * n_seg + seg) * net.K + k] = make_float2(clo[i] * pc[q][i], -clo[i] * pr[q][i]);
+      }
   }
+}
+
+int launch_screened_relax_sweep(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, hipStream_t s) {
+  launch_line_screen(net, n_box, ws, lay, kScreenForwardLower, s);
+  constexpr int Q = 2;
+  const int n_chunk = (net.K + 64 * Q - 1) / (64 * Q), n_tg = (lay.k5s_tiles + 3) / 4;
+  const int n_seg = sweep_segments(net, n_chunk * n_tg, lay.kc_bx);
+  const int per = (n_chunk * n_seg * n_tg + 7) / 8;
+  hipLaunchKernelGGL((k5p_sweep<Q, true>), dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, nullptr,
+                     n_chunk, n_tg, n_seg);
+  return n_seg;
 }
 
 // Per line: base-case penalty gradient + outage-sweep partials (as the line
@@ -603,6 +663,7 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
 __global__ __launch_bounds__(256) void k5r_lines(DevNet net, void* ws, WsLayout lay, int64_t box0,
                                                  const double* __restrict__ g_lo,
                                                  const double* __restrict__ g_hi, int sparse) {
+  // (sparse: the number of line segments, each with its per-outage sums)
   const int64_t b = box0 + blockIdx.y;
   const int l = blockIdx.x * 256 + threadIdx.x;
   if (l >= net.Lp) return;
@@ -634,9 +695,11 @@ __global__ __launch_bounds__(256) void k5r_lines(DevNet net, void* ws, WsLayout 
     }
     const int k = net.ctg_of_line[l];
     if (k >= 0) {
-      const float2 q = ws_ptr<float2>(ws, lay.cpart)[(size_t)b * net.K + k];
-      dc += q.x;
-      dr += q.y;
+      for (int t = 0; t < sparse; ++t) {
+        const float2 q = ws_ptr<float2>(ws, lay.cpart)[((size_t)b * sparse + t) * net.K + k];
+        dc += q.x;
+        dr += q.y;
+      }
     }
     gcf[l] = (float)dc;
     grf[l] = (float)dr;
@@ -928,6 +991,7 @@ void plan_backward(const DevNet& net, WsLayout& lay) {
 hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay,
                                   const float* box_lo, const float* box_hi, const double* g_lo, const double* g_hi, double* d_lo, double* d_hi,
                                   bool sparse, hipStream_t s, KernelTimer* tm) {
+  int n_seg = 0;
   sparse = sparse && !g_lo && g_hi && n_box >= kBatchMin && lay.batched && net.K > 0 && screen_fits(net, lay);
   if (sparse) {
     int t = tm->start(14, s);
@@ -935,9 +999,10 @@ hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, co
     tm->stop(t, s);
     t = tm->start(7, s);
     const int n_chunk = (net.K + 64 * kSparseQ - 1) / (64 * kSparseQ), n_tg = (lay.k5s_tiles + 3) / 4;
-    const int per = (n_chunk * n_tg + 7) / 8;
-    hipLaunchKernelGGL(k5p_sweep<kSparseQ>, dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, g_hi, n_chunk,
-                       n_tg);
+    n_seg = sweep_segments(net, n_chunk * n_tg, lay.k5_tiles);
+    const int per = (n_chunk * n_seg * n_tg + 7) / 8;
+    hipLaunchKernelGGL((k5p_sweep<kSparseQ, false>), dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, g_hi,
+                       n_chunk, n_tg, n_seg);
     tm->stop(t, s);
   } else if (n_box >= kBatchMin && lay.batched && net.K > 0) {
     const int t = tm->start(7, s);
@@ -966,7 +1031,7 @@ hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, co
     }
     const int t = tm->start(13, s);
     hipLaunchKernelGGL(k5r_lines, dim3((net.Lp + 255) / 256, nb), dim3(256), 0, s, net, ws, lay, b0, g_lo, g_hi,
-                       (int)sparse);
+                       n_seg);
     tm->stop(t, s);
   }
   if (n_box >= kBatchMin) {

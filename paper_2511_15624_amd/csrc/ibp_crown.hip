@@ -262,8 +262,9 @@ __device__ __forceinline__ size_t lv_index(const WsLayout& lay, const DevNet& ne
 
 // Per line: v, vabs >= |v_exact|, ev >= |v^ - v_exact|; block partials of the
 // limit total sum |s| t and of sum vabs.
+// (`sparse`: the counts are those of the screened sweep.)
 __global__ __launch_bounds__(256) void kc2_lines(DevNet net, void* ws, const void* wsr, WsLayout lay,
-                                                 int64_t box0) {
+                                                 int64_t box0, int sparse) {
   __shared__ double sh[4];
   const int64_t b = box0 + blockIdx.y;
   const int l = blockIdx.x * 256 + threadIdx.x;
@@ -279,7 +280,8 @@ __global__ __launch_bounds__(256) void kc2_lines(DevNet net, void* ws, const voi
       const double rf = ws_ptr<double>(ws, lay.lrf)[b * net.L + l];
       sb = (fabs(cf) - rf - fb > 0.0) ? copysign(1.0, cf) : 0.0;
     }
-    const int2 n = ws_ptr<int2>(ws, lay.ccnt)[b * net.Lp + l];
+    int2 n = ws_ptr<int2>(ws, lay.ccnt)[b * net.Lp + l];
+    if (sparse) n = make_int2(n.x - 2 * n.y, n.x);  // (all, negative)
     v = sb + (double)n.x;
     va = fabs(sb) + (double)n.y;
     T = fabs(sb) * fb + (double)n.y * net.fmax_c[l];
@@ -1267,9 +1269,12 @@ __global__ __launch_bounds__(256) void kc_ref_update(int64_t n, const float* __r
 // One relaxation pass over every box; wsr != nullptr takes the slopes at the
 // reference points whose forward data it holds.
 static void relax_pass(const DevNet& net, int64_t n_box, const float* lo, const float* hi, double* f_hi,
-                       double* crown, float* vertex, void* ws, const void* wsr, int again, const WsLayout& lay,
+                       double* crown, float* vertex, void* ws, const void* wsr, int again, const WsLayout& plan,
                        hipStream_t s, KernelTimer* tm) {
   const bool ref = wsr != nullptr;
+  const int sparse = plan.rscreen && !ref;
+  WsLayout lay = plan;
+
   for (int64_t b0 = 0; b0 < n_box; b0 += 65535) {
     const int nb = (int)std::min<int64_t>(65535, n_box - b0);
     const int t = tm->start(10, s);
@@ -1289,7 +1294,9 @@ static void relax_pass(const DevNet& net, int64_t n_box, const float* lo, const 
   if (net.K > 0 && n_box >= kCB) {
     const int t = tm->start(10, s);
     const dim3 grid(tiles, lay.kc_bx, (net.K + kKPB - 1) / kKPB);
-    if (ref)
+    if (sparse)
+      lay.kc_bx = launch_screened_relax_sweep(net, n_box, ws, lay, s);
+    else if (ref)
       hipLaunchKernelGGL(kc1b_sweep<true>, grid, dim3(256), 0, s, net, ws, wsr, lay, n_box);
     else
       hipLaunchKernelGGL(kc1b_sweep<false>, grid, dim3(256), 0, s, net, ws, wsr, lay, n_box);
@@ -1298,7 +1305,7 @@ static void relax_pass(const DevNet& net, int64_t n_box, const float* lo, const 
   for (int64_t b0 = 0; b0 < n_box; b0 += 65535) {
     const int nb = (int)std::min<int64_t>(65535, n_box - b0);
     const int t = tm->start(11, s);
-    hipLaunchKernelGGL(kc2_lines, dim3(lay.n_ct, nb), dim3(256), 0, s, net, ws, wsr, lay, b0);
+    hipLaunchKernelGGL(kc2_lines, dim3(lay.n_ct, nb), dim3(256), 0, s, net, ws, wsr, lay, b0, sparse);
     if (n_box < kCB)
       hipLaunchKernelGGL(kc3_ptdf_t, dim3(lay.kc3_bx, lay.kc3_by, nb), dim3(256), 0, s, net, ws, lay, b0);
     tm->stop(t, s);

@@ -105,6 +105,7 @@ struct WsLayout {
   // screened backward sweep of the gradient of f_hi (box-tiled calls): the
   // lines that may hold an active lower-penalty element, per tile of boxes
   int k5s_tiles = 0;               // tiles of kScreenBoxes boxes (0: not laid out)
+  int rscreen = 0;                 // the upper relaxation's slopes by the screened sweep
   int fscreen = 0;                 // one-sided box-tiled forward calls take the screened sweep
   size_t smask = 0;                // uint64 [tiles][Lp / 64]: candidate-line bit masks
   size_t srec = 0;                 // float [tiles][Lp][12]: the tile's boxes' centres and radius terms

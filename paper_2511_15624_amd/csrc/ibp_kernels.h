@@ -69,6 +69,12 @@ struct Tune {
 constexpr int kScreenBoxes = 4;
 constexpr int kSparseQ = 4;
 constexpr int kSparseMaxWords = 512;  // networks up to 32768 lines
+// Segments the screened sweeps split a tile's marked lines into, so that about
+// 1024 blocks (of `blocks` per segment) share a call of few boxes; each segment
+// needs a slot for its sums (`slots`) and at least one 64-line mask word.
+inline int sweep_segments(const DevNet& net, int blocks, int slots) {
+  return std::max(1, std::min(std::min(1024 / std::max(1, blocks), slots), net.Lp / 64));
+}
 // What a screen bounds: the lower penalties with the backward's unpadded
 // radii (gradient of f_hi), or the forward's padded lower / upper penalties
 // (one-sided bound f_hi / f_lo).
@@ -114,6 +120,10 @@ hipError_t launch_lin_pack(const DevNet& net, int8_t* dig, int8_t* dga, float* s
 // The outage penalties of lay.sides for every box, after the line epilogue.
 hipError_t launch_linear_sweep(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, hipStream_t s,
                                KernelTimer* tm);
+// The slopes of the upper relaxation over the lines that the lower-penalty
+// screen marks (lay.rscreen): per-line counts, as uint64 (negative << 32 | all),
+// in lay.ccnt (zeroed before); returns the number of per-outage partials in lay.cv.
+int launch_screened_relax_sweep(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, hipStream_t s);
 bool tune_valid(const Tune& t);
 bool tune_batched_valid(const Tune& t);
 int batched_rows_rule(const DevNet& net, int k3_bx, int64_t groups);

@@ -29,6 +29,7 @@
 // which the sweeps read by scalar loads.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <cstdint>
@@ -42,13 +43,20 @@ namespace ibp {
 
 constexpr int kScreenChunk = 128;  // outages per LDS chunk of the screen
 
-// Tiles per screen block: 16 share every factor load when that still gives
-// about two blocks per CU (4096 boxes at 2000 buses: 0.69 ms; 32 tiles gave
-// too few blocks, 1.30 ms), otherwise 4 (1024 boxes: 16 tiles left the chip
-// under-filled with 208 blocks).
+// Tiles per screen block (they share every factor load), and the outage ranges a
+// line block and tile group is split over when those alone leave the chip idle:
+// partial maxima then meet in the first word of the tile's line record, and
+// k5s_mark takes the marks from there.  About kScreenBlocks blocks (2000 buses:
+// 8 boxes 600 -> 30 us, 1024 boxes 0.42 -> 0.21 ms; from 4096 boxes on, 0.72 ms, no
+// split is needed).
+constexpr int kScreenBlocks = 1024;
 inline int screen_tiles(const DevNet& net, const WsLayout& lay) {
-  const int64_t line_blocks = (net.Lp + 255) / 256;
-  return ((int64_t)lay.k5s_tiles + 15) / 16 * line_blocks >= 512 ? 16 : 4;
+  return ((int64_t)lay.k5s_tiles + 15) / 16 * ((net.Lp + 255) / 256) >= 64 ? 16 : 4;
+}
+inline int screen_splits(const DevNet& net, const WsLayout& lay) {
+  const int g = screen_tiles(net, lay);
+  const int64_t blocks = (int64_t)((lay.k5s_tiles + g - 1) / g) * ((net.Lp + 255) / 256);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kScreenBlocks / blocks, (net.K + kScreenChunk - 1) / kScreenChunk));
 }
 
 // The per-outage (centre, radius) the sweep of `mode` uses: the backward's
@@ -86,7 +94,7 @@ __device__ __forceinline__ float line_g(const DevNet& net, void* ws, const WsLay
 // K5w: per tile and outage W (zero past the last outage); per tile and block
 // of 256 outages the largest |c_c| + r_c, for the margin.
 template <int MODE>
-__global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
+__global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayout lay, int64_t n_box, int clear) {
   constexpr int S = kScreenBoxes;
   __shared__ unsigned zs[4];
   const int k = blockIdx.x * 256 + threadIdx.x;
@@ -104,6 +112,9 @@ __global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayo
     }
   }
   if (k < net.Kp) ws_ptr<float>(ws, lay.sw)[t * net.Kp + k] = wv;
+  if (clear)  // the partial maxima's slots
+    for (int l = k; l < net.Lp; l += gridDim.x * 256)
+      ws_ptr<float>(ws, lay.srec)[((size_t)t * net.Lp + l) * kScreenRecFloats] = 0.0f;
   // non-negative floats order like their bit patterns
   const unsigned zb = wave_max_u32(__float_as_uint(z));
   if ((threadIdx.x & 63) == 0) zs[threadIdx.x >> 6] = zb;
@@ -113,23 +124,70 @@ __global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayo
         __uint_as_float(max(max(zs[0], zs[1]), max(zs[2], zs[3])));
 }
 
-// K5s: one line per lane, G tiles per block, the tiles' W staged
-// in LDS kScreenChunk outages at a time.
-template <int MODE, int G>
-__global__ __launch_bounds__(256) void k5s_screen(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
+// One line's mark in one tile from the largest |Lam| W of its outages: every lane
+// of the block's waves calls it with its own line (`lon`: a real line), wave-uniform
+// tile and margin scale z.
+template <int MODE>
+__device__ __forceinline__ void mark_line(const DevNet& net, void* ws, const WsLayout& lay, int64_t n_box, int64_t t,
+                                          int l, bool lon, float m, float z, float fc, float amax) {
   constexpr int S = kScreenBoxes;
   static_assert(S == 4, "a tile's line record holds four boxes");
+  // a box past the end gets a record that never tests active
+  constexpr float kOff = MODE >= kScreenForwardUpper ? -INFINITY : INFINITY;
+  const float* lc = ws_ptr<float>(ws, lay.lc);
+  const int words = net.Lp / 64, word = l >> 6;
+  float cv[S], rv[S], gv[S];
+  float base = -FLT_MAX, sc = 0.0f;
+#pragma unroll
+  for (int i = 0; i < S; ++i) {
+    const int64_t b = t * S + i;
+    cv[i] = 0.0f;
+    rv[i] = kOff;
+    gv[i] = INFINITY;
+    if (lon && b < n_box) {
+      cv[i] = lc[b * net.Lp + l];
+      rv[i] = line_term<MODE>(net, ws, lay, b, l, fc);
+      base = fmaxf(base, MODE >= kScreenForwardUpper ? fabsf(cv[i]) + rv[i] : fabsf(cv[i]) - rv[i]);
+      sc = fmaxf(sc, fabsf(cv[i]) + fabsf(rv[i]));
+    }
+  }
+  const float margin = 0x1p-19f * (sc + amax * z);
+  const bool flag = lon && base + m > -margin;
+  const uint64_t bits = __builtin_amdgcn_ballot_w64(flag);
+  if ((threadIdx.x & 63) == 0 && word < words) ws_ptr<uint64_t>(ws, lay.smask)[t * words + word] = bits;
+  if (!flag) return;
+  float4* rec = reinterpret_cast<float4*>(ws_ptr<float>(ws, lay.srec) + ((size_t)t * net.Lp + l) * kScreenRecFloats);
+  rec[0] = make_float4(cv[0], cv[1], cv[2], cv[3]);
+  rec[1] = make_float4(rv[0], rv[1], rv[2], rv[3]);
+  if (MODE == kScreenForwardBoth) {
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+      if (t * S + i < n_box) gv[i] = line_g(net, ws, lay, t * S + i, l);
+    rec[2] = make_float4(gv[0], gv[1], gv[2], gv[3]);
+  }
+  if (MODE == kScreenBackwardLower) {
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+      if (t * S + i < n_box) ws_ptr<uint64_t>(ws, lay.lcnt)[(t * S + i) * net.Lp + l] = 0ull;
+  }
+}
+
+// K5s: one line per lane, G tiles per block, the tiles' W staged in LDS
+// kScreenChunk outages at a time; outage range blockIdx.z of gridDim.z.
+template <int MODE, int G>
+__global__ __launch_bounds__(256) void k5s_screen(DevNet net, void* ws, WsLayout lay, int64_t n_box, int k_per) {
   static_assert(G % 4 == 0, "tiles are read from LDS as float4");
   __shared__ __align__(16) float wsh[kScreenChunk][G];
   __shared__ float zsh[G];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x;
   const int l = blockIdx.x * 256 + tid;
   const bool lon = l < net.L;
   const int lq = min(l, net.Lp - 1);
   const int64_t tile0 = (int64_t)blockIdx.y * G;
   const int ntile = (int)min<int64_t>(G, lay.k5s_tiles - tile0);
+  const int kbeg = blockIdx.z * k_per, kend = min(net.K, kbeg + k_per);
   const float* W = ws_ptr<float>(ws, lay.sw) + tile0 * net.Kp;
-  if (tid < G) {
+  if (tid < G && gridDim.z == 1) {
     float z = 0.0f;
     if (tid < ntile)
       for (int j = 0; j < lay.k5w_bx; ++j) z = fmaxf(z, ws_ptr<float>(ws, lay.sz)[(tile0 + tid) * lay.k5w_bx + j]);
@@ -139,8 +197,8 @@ __global__ __launch_bounds__(256) void k5s_screen(DevNet net, void* ws, WsLayout
 #pragma unroll
   for (int g = 0; g < G; ++g) m[g] = 0.0f;
   const float* lam = net.lodf + lq;
-  for (int k0 = 0; k0 < net.K; k0 += kScreenChunk) {
-    const int nk = min(kScreenChunk, net.K - k0);
+  for (int k0 = kbeg; k0 < kend; k0 += kScreenChunk) {
+    const int nk = min(kScreenChunk, kend - k0);
     __syncthreads();
     for (int idx = tid; idx < kScreenChunk * G; idx += 256) {
       const int kk = idx % kScreenChunk, g = idx / kScreenChunk;
@@ -166,65 +224,50 @@ __global__ __launch_bounds__(256) void k5s_screen(DevNet net, void* ws, WsLayout
       }
     }
   }
+  if (gridDim.z > 1) {  // non-negative floats order like their bit patterns
+    if (lon)
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        if (g < ntile)
+          atomicMax(reinterpret_cast<unsigned*>(ws_ptr<float>(ws, lay.srec) +
+                                                ((size_t)(tile0 + g) * net.Lp + l) * kScreenRecFloats),
+                    __float_as_uint(m[g]));
+    return;
+  }
   const float fc = lon ? net.fmax_c32[l] : 0.0f;
   const float amax = lon ? net.lam_max[l] : 0.0f;
-  const float* lc = ws_ptr<float>(ws, lay.lc);
-  const int words = net.Lp / 64;
-  const int word = blockIdx.x * 4 + w;
-  // a box past the end gets a record that never tests active
-  constexpr float kOff = MODE >= kScreenForwardUpper ? -INFINITY : INFINITY;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     if (g >= ntile) break;  // uniform
-    const int64_t t = tile0 + g;
-    float cv[S], rv[S], gv[S];
-    float base = -FLT_MAX, sc = 0.0f;
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-      const int64_t b = t * S + i;
-      cv[i] = 0.0f;
-      rv[i] = kOff;
-      gv[i] = INFINITY;
-      if (lon && b < n_box) {
-        cv[i] = lc[b * net.Lp + l];
-        rv[i] = line_term<MODE>(net, ws, lay, b, l, fc);
-        base = fmaxf(base, MODE >= kScreenForwardUpper ? fabsf(cv[i]) + rv[i] : fabsf(cv[i]) - rv[i]);
-        sc = fmaxf(sc, fabsf(cv[i]) + fabsf(rv[i]));
-      }
-    }
-    const float margin = 0x1p-19f * (sc + amax * zsh[g]);
-    const bool flag = lon && base + m[g] > -margin;
-    const uint64_t bits = __builtin_amdgcn_ballot_w64(flag);
-    if (lane == 0 && word < words) ws_ptr<uint64_t>(ws, lay.smask)[t * words + word] = bits;
-    if (flag) {
-      float4* rec = reinterpret_cast<float4*>(ws_ptr<float>(ws, lay.srec) + ((size_t)t * net.Lp + l) * kScreenRecFloats);
-      rec[0] = make_float4(cv[0], cv[1], cv[2], cv[3]);
-      rec[1] = make_float4(rv[0], rv[1], rv[2], rv[3]);
-      if (MODE == kScreenForwardBoth) {
-#pragma unroll
-        for (int i = 0; i < S; ++i)
-          if (lon && t * S + i < n_box) gv[i] = line_g(net, ws, lay, t * S + i, l);
-        rec[2] = make_float4(gv[0], gv[1], gv[2], gv[3]);
-      }
-      if (MODE == kScreenBackwardLower) {
-#pragma unroll
-        for (int i = 0; i < S; ++i)
-          if (t * S + i < n_box) ws_ptr<uint64_t>(ws, lay.lcnt)[(t * S + i) * net.Lp + l] = 0ull;
-      }
-    }
+    mark_line<MODE>(net, ws, lay, n_box, tile0 + g, l, lon, m[g], zsh[g], fc, amax);
   }
+}
+
+// The marks of a screen that was split over the outages: one tile per block row.
+template <int MODE>
+__global__ __launch_bounds__(256) void k5s_mark(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
+  const int l = blockIdx.x * 256 + threadIdx.x;
+  const int64_t t = blockIdx.y;
+  const bool lon = l < net.L;
+  float z = 0.0f;
+  for (int j = 0; j < lay.k5w_bx; ++j) z = fmaxf(z, ws_ptr<float>(ws, lay.sz)[t * lay.k5w_bx + j]);
+  const float m = lon ? ws_ptr<float>(ws, lay.srec)[((size_t)t * net.Lp + l) * kScreenRecFloats] : 0.0f;
+  mark_line<MODE>(net, ws, lay, n_box, t, l, lon, m, z, lon ? net.fmax_c32[l] : 0.0f, lon ? net.lam_max[l] : 0.0f);
 }
 
 template <int MODE>
 static void launch_screen_mode(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, hipStream_t s) {
-  hipLaunchKernelGGL(k5w_tile_max<MODE>, dim3(lay.k5w_bx, lay.k5s_tiles), dim3(256), 0, s, net, ws, lay, n_box);
-  const unsigned gx = (net.Lp + 255) / 256;
-  if (screen_tiles(net, lay) == 16)
-    hipLaunchKernelGGL((k5s_screen<MODE, 16>), dim3(gx, (lay.k5s_tiles + 15) / 16), dim3(256), 0, s, net, ws, lay,
-                       n_box);
+  const int z = screen_splits(net, lay), g = screen_tiles(net, lay);
+  const int k_per = ((net.K + z - 1) / z + kScreenChunk - 1) / kScreenChunk * kScreenChunk;
+  const unsigned gx = (net.Lp + 255) / 256, gz = (unsigned)((net.K + k_per - 1) / k_per);
+  hipLaunchKernelGGL(k5w_tile_max<MODE>, dim3(lay.k5w_bx, lay.k5s_tiles), dim3(256), 0, s, net, ws, lay, n_box,
+                     (int)(gz > 1));
+  const dim3 grid(gx, (lay.k5s_tiles + g - 1) / g, gz);
+  if (g == 16)
+    hipLaunchKernelGGL((k5s_screen<MODE, 16>), grid, dim3(256), 0, s, net, ws, lay, n_box, k_per);
   else
-    hipLaunchKernelGGL((k5s_screen<MODE, 4>), dim3(gx, (lay.k5s_tiles + 3) / 4), dim3(256), 0, s, net, ws, lay,
-                       n_box);
+    hipLaunchKernelGGL((k5s_screen<MODE, 4>), grid, dim3(256), 0, s, net, ws, lay, n_box, k_per);
+  if (gz > 1) hipLaunchKernelGGL(k5s_mark<MODE>, dim3(gx, lay.k5s_tiles), dim3(256), 0, s, net, ws, lay, n_box);
 }
 
 void launch_line_screen(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, int mode, hipStream_t s) {
@@ -244,30 +287,32 @@ void launch_line_screen(const DevNet& net, int64_t n_box, void* ws, const WsLayo
 // (the same float32 operations on the same values), and each line's Q
 // elements per box are summed in float32 (depth 2, within the depth-3 sums
 // the padding of the outage-penalty total allows) and added in float64.
-// Per (box, chunk of 64 Q outages) one float64 partial, in the slot the
-// finalize sums; slots past the last chunk are cleared.
+// Per (box, chunk of 64 Q outages, line segment) one float64 partial, in the slot
+// the finalize sums; slots past the last one are cleared.  The lines are walked in
+// n_seg segments, a wave each, where tiles and chunks give few waves (sweep_segments).
 template <int SIDES, int Q>
 __global__ __launch_bounds__(256) void k3p_sweep(DevNet net, void* ws, WsLayout lay, int64_t n_box, int n_chunk,
-                                                 int n_tg) {
+                                                 int n_tg, int n_seg) {
   constexpr int S = kScreenBoxes;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // unit u = (chunk, group of 4 tiles: one per wave), chunk-major, and the
   // blocks of one XCD (block id mod 8) on consecutive units
-  const int U = n_chunk * n_tg;
+  const int U = n_chunk * n_seg * n_tg;
   const int per = (U + 7) / 8;
   const int slot = blockIdx.x >> 3;
   const int u = (blockIdx.x & 7) * per + slot;
   if (slot >= per || u >= U) return;  // the whole block
   const int tile = (u % n_tg) * 4 + w;
   const bool on = tile < lay.k5s_tiles;
-  const int chunk = u / n_tg;
+  const int seg = (u / n_tg) % n_seg, chunk = u / n_tg / n_seg;
   const int kw = chunk * 64 * Q;
   __shared__ uint64_t smk_all[4][kSparseMaxWords];
   uint64_t* smk = smk_all[w];
-  const int words = net.Lp / 64;
+  const int per_seg = (net.Lp / 64 + n_seg - 1) / n_seg, word0 = seg * per_seg;
+  const int words = min(per_seg, net.Lp / 64 - word0);  // of this segment (may be none)
   if (on) {
-    const uint64_t* mask = ws_ptr<uint64_t>(ws, lay.smask) + (size_t)tile * words;
+    const uint64_t* mask = ws_ptr<uint64_t>(ws, lay.smask) + (size_t)tile * (net.Lp / 64) + word0;
     for (int j = lane; j < words; j += 64) smk[j] = mask[j];
   }
   __syncthreads();
@@ -337,7 +382,7 @@ __global__ __launch_bounds__(256) void k3p_sweep(DevNet net, void* ws, WsLayout 
              (unsigned)__builtin_amdgcn_readlane((int)(unsigned)mw, i);
       ++j;
     }
-    const int l = (j - 1) * 64 + __builtin_ctzll(bits);
+    const int l = (word0 + j - 1) * 64 + __builtin_ctzll(bits);
     bits &= bits - 1;
     return l;
   };
@@ -368,9 +413,9 @@ __global__ __launch_bounds__(256) void k3p_sweep(DevNet net, void* ws, WsLayout 
     const double t = wave_sum(acc[i]);
     const double t2 = SIDES == 3 ? wave_sum(acc2[i]) : 0.0;
     if (lane == 0 && b0 + i < n_box) {
-      p3[(b0 + i) * lay.n_p3 + chunk] = SIDES == 1 ? make_double2(0.0, t) : make_double2(t, t2);
-      if (chunk == 0)
-        for (int c = n_chunk; c < lay.n_p3; ++c) p3[(b0 + i) * lay.n_p3 + c] = make_double2(0.0, 0.0);
+      p3[(b0 + i) * lay.n_p3 + chunk * n_seg + seg] = SIDES == 1 ? make_double2(0.0, t) : make_double2(t, t2);
+      if (chunk == 0 && seg == 0)
+        for (int c = n_chunk * n_seg; c < lay.n_p3; ++c) p3[(b0 + i) * lay.n_p3 + c] = make_double2(0.0, 0.0);
     }
   }
 }
@@ -378,13 +423,17 @@ __global__ __launch_bounds__(256) void k3p_sweep(DevNet net, void* ws, WsLayout 
 void launch_screened_forward_sweep(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, int sides,
                                    hipStream_t s) {
   const int n_chunk = (net.K + 64 * kSparseQ - 1) / (64 * kSparseQ), n_tg = (lay.k5s_tiles + 3) / 4;
-  const int per = (n_chunk * n_tg + 7) / 8;
+  const int n_seg = sweep_segments(net, n_chunk * n_tg, lay.n_p3 / n_chunk);
+  const int per = (n_chunk * n_seg * n_tg + 7) / 8;
   if (sides == 1)
-    hipLaunchKernelGGL((k3p_sweep<1, kSparseQ>), dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, n_chunk, n_tg);
+    hipLaunchKernelGGL((k3p_sweep<1, kSparseQ>), dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, n_chunk, n_tg,
+                       n_seg);
   else if (sides == 2)
-    hipLaunchKernelGGL((k3p_sweep<2, kSparseQ>), dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, n_chunk, n_tg);
+    hipLaunchKernelGGL((k3p_sweep<2, kSparseQ>), dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, n_chunk, n_tg,
+                       n_seg);
   else
-    hipLaunchKernelGGL((k3p_sweep<3, kSparseQ>), dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, n_chunk, n_tg);
+    hipLaunchKernelGGL((k3p_sweep<3, kSparseQ>), dim3(8 * per), dim3(256), 0, s, net, ws, lay, n_box, n_chunk, n_tg,
+                       n_seg);
 }
 
 }  // namespace ibp
