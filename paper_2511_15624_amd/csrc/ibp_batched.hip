@@ -176,6 +176,83 @@ __global__ __launch_bounds__(256, 2) void k2b_base_flows_mfma(DevNet net, void* 
   }
 }
 
+// The same sums, in the same order (a line's float32 flow then rounds alike), where
+// 64-line x 32-box tiles give few waves: the eight waves of a block take the centres
+// and the radii of four 16-line x 16-box tiles, one chain of matrix products each,
+// over operands that the block loads three stages ahead and shares in LDS.  With few
+// waves the plain kernel waits about 0.6 us per four-bus step: 500 buses, 37 boxes 80
+// -> 18 us, 512 boxes 88 -> 31; 2000 buses, 4 boxes 50 -> 20 us, 128 boxes 97 -> 91;
+// 8316 buses, 4 boxes 312 -> 183 us.  From about 2560 of these blocks on the plain
+// kernel's wider tiles win: 2000 buses, 256 boxes (4928 blocks) 157 against 180 us,
+// 8316 buses, 32 boxes (3264) 339 against 373.
+constexpr int kThinBuses = 32;  // buses of a stage: a phi quad and an injection pair per thread
+constexpr int kThinRow = 64 + 16;  // floats of a phi row in LDS: a wave's four rows meet all 64 banks
+constexpr int64_t kThinBlocks = 2560;
+
+__global__ __launch_bounds__(512) void k2b_base_flows_thin(DevNet net, void* ws, WsLayout lay, int64_t n_box,
+                                                           const double2* __restrict__ inj_all) {
+  __shared__ float4 sp[2][kThinBuses * kThinRow / 4];
+  __shared__ double sc[2][2][kThinBuses * 16];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int rad = w & 1, lt = w >> 1;
+  const int l0 = blockIdx.x * 64;
+  const int i16 = lane & 15, k4 = lane >> 4;
+  const int64_t b0 = (int64_t)blockIdx.y * 16, b = b0 + i16;
+  const int nb0 = blockIdx.z * lay.k2_chunk;
+  const int nb1 = min(net.N, nb0 + lay.k2_chunk);
+  if (nb0 >= nb1) return;  // the whole block
+  const int n_last = (nb1 - 1) | 3;  // injections are padded to whole steps, PTDF rows clamped
+  const int N = net.N, Lp4 = net.Lp / 4;
+  const int rown = t >> 4, col = t & 15;  // this thread's bus of a stage, its lines' quad and its box
+  const float4* pa = reinterpret_cast<const float4*>(net.phiT + l0) + col;
+  const double2* pb = inj_all + min(b0 + col, n_box - 1) * net.Np;
+  auto load = [&](float4& x, double2& c, int n0) {
+    const int n = min(n0 + rown, n_last);
+    x = pa[(size_t)min(n, N - 1) * Lp4];
+    c = pb[n];
+  };
+  v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
+  int buf = 0;
+  auto stage = [&](float4& x, double2& c, int n0) {
+    sp[buf][rown * (kThinRow / 4) + col] = x;
+    sc[buf][0][t] = c.x;
+    sc[buf][1][t] = c.y;
+    load(x, c, n0 + 3 * kThinBuses);
+    __syncthreads();
+    const float* fp = reinterpret_cast<const float*>(sp[buf]) + k4 * kThinRow + lt * 16 + i16;
+    const double* fc = sc[buf][rad] + k4 * 16 + i16;
+    float xs[kThinBuses / 4];
+    double cs[kThinBuses / 4];
+#pragma unroll
+    for (int u = 0; u < kThinBuses / 4; ++u) {
+      xs[u] = fp[4 * u * kThinRow];
+      cs[u] = fc[64 * u];
+    }
+#pragma unroll
+    for (int u = 0; u < kThinBuses / 4; ++u)
+      if (n0 + 4 * u < nb1) {
+        const double a = (double)xs[u];
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(rad ? fabs(a) : a, cs[u], acc, 0, 0, 0);
+      }
+    buf ^= 1;  // the other buffer was read before this stage's barrier
+  };
+  float4 x0, x1, x2;
+  double2 c0, c1, c2;
+  load(x0, c0, nb0);
+  load(x1, c1, nb0 + kThinBuses);
+  load(x2, c2, nb0 + 2 * kThinBuses);
+  for (int n0 = nb0; n0 < nb1; n0 += 3 * kThinBuses) {
+    stage(x0, c0, n0);
+    stage(x1, c1, n0 + kThinBuses);
+    stage(x2, c2, n0 + 2 * kThinBuses);
+  }
+  if (b >= n_box) return;
+  double* out = reinterpret_cast<double*>(ws_ptr<double2>(ws, lay.part2) +
+                                          ((size_t)b * lay.k2_by + blockIdx.z) * net.Lp + l0 + lt * 16) + rad;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) out[2 * (4 * r + k4)] = acc[r];
+}
+
 // Outage sweep for kBT boxes x 256 lines per wave over one block row of outages.
 // SIDES as in k3_elem: one-sided calls compute only the penalty bound they need.
 //
@@ -365,7 +442,11 @@ hipError_t launch_batched_sweeps(const DevNet& net, int64_t n_box, void* ws, con
   if (phase == 0) {
     const int t = tm->start(5, s);
     const double2* inj = reinterpret_cast<const double2*>(static_cast<char*>(ws) + lay.inj);
-    if (lay.k2_mfma)
+    const int64_t thin = (int64_t)(net.Lp / 64) * ((n_box + 15) / 16) * lay.k2_by;
+    if (lay.k2_mfma && thin <= kThinBlocks)
+      hipLaunchKernelGGL(k2b_base_flows_thin, dim3(net.Lp / 64, (unsigned)((n_box + 15) / 16), (unsigned)lay.k2_by),
+                         dim3(512), 0, s, net, ws, lay, n_box, inj);
+    else if (lay.k2_mfma)
       hipLaunchKernelGGL(k2b_base_flows_mfma,
                          dim3((net.Lp / 64 + 3) / 4, (unsigned)((n_box + 31) / 32), (unsigned)lay.k2_by), dim3(256),
                          0, s, net, ws, lay, n_box, inj);
