@@ -250,22 +250,34 @@ __device__ __forceinline__ void k5b_step(const float4 (&x)[4], const float2 (&q)
 // MODE 1 / 2: the caller asked for the gradient of f_hi / f_lo alone (the
 // other weight pointer is null), so only that side's code is compiled into
 // the kernel (fewer registers, more waves); MODE 3 picks the sides per wave.
-template <int MODE>
-__global__ __launch_bounds__(256) void k5b_outage_vjp(DevNet net, void* ws, WsLayout lay, int64_t n_box,
+//
+// SPLIT, for calls whose line tiles, outage rows and box tiles give few waves: the
+// eight waves of a block share one box tile and one outage row, each sweeps an
+// eighth of it, and their line sums meet in LDS.  One wave takes 128 steps of
+// about 2.7 us otherwise: 500 buses, 37 boxes 353 -> 63 us, 1024 boxes (1536 tiles of
+// boxes, lines and outage rows) 446 -> 329; 150 buses, 500 boxes 154 -> 35 us; 8316
+// buses, 4 boxes 423 -> 259 us.  With more tiles the chip is full and the plain form's
+// shared factor rows win: 500 buses, 2048 boxes (3072 tiles) 493 against 730 us.
+constexpr int64_t kK5SplitTiles = 1536;
+
+template <int MODE, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 512 : 256) void k5b_outage_vjp(DevNet net, void* ws, WsLayout lay, int64_t n_box,
                                                       const double* __restrict__ g_lo,
                                                       const double* __restrict__ g_hi,
                                                       const float2* __restrict__ cb_all,
                                                       float2* __restrict__ cpart_all) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t b0 = ((int64_t)blockIdx.z * 4 + w) * kBT5;
+  const int64_t b0 = (SPLIT ? (int64_t)blockIdx.z : (int64_t)blockIdx.z * 4 + w) * kBT5;
   if (b0 >= n_box) return;
   const int tile = blockIdx.x;
   const int col = tile * 64 + lane;
   const int Lp4 = net.Lp / 4;
   const bool on = col < Lp4;
-  const int k0 = blockIdx.y * kK5ChunkTiled;
-  const int k1 = min(net.K, k0 + kK5ChunkTiled);
+  const int row0 = blockIdx.y * kK5ChunkTiled, row1 = min(net.K, row0 + kK5ChunkTiled);
+  const int per = SPLIT ? ((row1 - row0 + 31) / 32) * 4 : kK5ChunkTiled;  // whole steps of four
+  const int k0 = SPLIT ? row0 + w * per : row0;
+  const int k1 = min(row1, k0 + per);
   int64_t bb[kBT5];
   float chi[kBT5], clo[kBT5];
   float4 c4[kBT5], rm4[kBT5], rp4[kBT5];
@@ -410,14 +422,42 @@ __global__ __launch_bounds__(256) void k5b_outage_vjp(DevNet net, void* ws, WsLa
       }
     }
   };
-  if (MODE != 3)
-    sweep(std::integral_constant<int, MODE>());
-  else if (no_hi)
-    sweep_guarded(std::integral_constant<int, 1>());
-  else if (no_lo)
-    sweep_guarded(std::integral_constant<int, 2>());
-  else
-    sweep_guarded(std::integral_constant<int, 3>());
+  auto go = [&] {
+    if (MODE != 3)
+      sweep(std::integral_constant<int, MODE>());
+    else if (no_hi)
+      sweep_guarded(std::integral_constant<int, 1>());
+    else if (no_lo)
+      sweep_guarded(std::integral_constant<int, 2>());
+    else
+      sweep_guarded(std::integral_constant<int, 3>());
+  };
+  if constexpr (SPLIT) {
+    if (k0 < k1) go();  // parts beyond the last outage are empty
+  } else {
+    go();
+  }
+  if constexpr (SPLIT) {
+    // line j of a lane at a time; wave w finishes box w / 2, field w % 2
+    __shared__ float sh[8][8][64];
+    float* lp = ws_ptr<float>(ws, lay.lpart) +
+                2 * (((size_t)min(b0 + (w >> 1), n_box - 1) * lay.k5_by + blockIdx.y) * net.Lp + 4 * col) + (w & 1);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kBT5; ++i) {
+        sh[w][2 * i][lane] = gc[i][j];
+        sh[w][2 * i + 1][lane] = gr[i][j];
+      }
+      __syncthreads();
+      float t = 0.0f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t += sh[u][w][lane];
+      if (on && b0 + (w >> 1) < n_box) lp[2 * j] = t;
+    }
+    return;
+  }
   if (on) {
 #pragma unroll
     for (int i = 0; i < kBT5; ++i) {
@@ -706,6 +746,7 @@ __global__ __launch_bounds__(256) void k5r_lines(DevNet net, void* ws, WsLayout 
     return;
   }
   const float2* lp = ws_ptr<float2>(ws, lay.lpart) + (size_t)b * lay.k5_by * net.Lp + l;
+#pragma unroll 8
   for (int y = 0; y < lay.k5_by; ++y) {
     const float2 t = lp[(size_t)y * net.Lp];
     dc += t.x;
@@ -714,6 +755,7 @@ __global__ __launch_bounds__(256) void k5r_lines(DevNet net, void* ws, WsLayout 
   const int k = net.ctg_of_line[l];
   if (k >= 0) {
     const float2* cp = ws_ptr<float2>(ws, lay.cpart) + (size_t)b * lay.k5_tiles * net.K + k;
+#pragma unroll 8
     for (int t = 0; t < lay.k5_tiles; ++t) {
       const float2 q = cp[(size_t)t * net.K];
       dc += q.x;
@@ -868,6 +910,38 @@ __global__ __launch_bounds__(256) void k6b_ptdf_t_tiled(DevNet net, void* ws, Ws
 typedef float v16f __attribute__((ext_vector_type(16)));
 constexpr int kMB = 64, kMN = 64;
 
+__device__ __forceinline__ void k6m_chunk(const float4* pc, const float4* pr, const float4* pp, int l0, double (&sc)[16],
+                                          double (&sr)[16]) {
+  float4 a[4], r[4], p[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    a[u] = pc[(l0 + 8 * u) / 4];
+    r[u] = pr[(l0 + 8 * u) / 4];
+    p[u] = pp[(l0 + 8 * u) / 4];
+  }
+  // all twelve loads of the chunk in flight before its first MFMA (the
+  // compiler would otherwise issue each step's loads after the previous
+  // step's MFMAs and wait on them one step at a time)
+  __builtin_amdgcn_sched_barrier(0);
+  v16f ac = {}, ar = {};
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    ac = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].x, p[u].x, ac, 0, 0, 0);
+    ar = __builtin_amdgcn_mfma_f32_32x32x2f32(r[u].x, fabsf(p[u].x), ar, 0, 0, 0);
+    ac = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].y, p[u].y, ac, 0, 0, 0);
+    ar = __builtin_amdgcn_mfma_f32_32x32x2f32(r[u].y, fabsf(p[u].y), ar, 0, 0, 0);
+    ac = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].z, p[u].z, ac, 0, 0, 0);
+    ar = __builtin_amdgcn_mfma_f32_32x32x2f32(r[u].z, fabsf(p[u].z), ar, 0, 0, 0);
+    ac = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].w, p[u].w, ac, 0, 0, 0);
+    ar = __builtin_amdgcn_mfma_f32_32x32x2f32(r[u].w, fabsf(p[u].w), ar, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    sc[e] += (double)ac[e];
+    sr[e] += (double)ar[e];
+  }
+}
+
 __global__ __launch_bounds__(256) void k6m_ptdf_t_mfma(DevNet net, void* ws, WsLayout lay, int64_t n_box, int n_bt,
                                                       int n_nt) {
   const int id = blockIdx.x;
@@ -886,36 +960,7 @@ __global__ __launch_bounds__(256) void k6m_ptdf_t_mfma(DevNet net, void* ws, WsL
   double sc[16], sr[16];
 #pragma unroll
   for (int e = 0; e < 16; ++e) sc[e] = sr[e] = 0.0;
-  for (int l0 = 0; l0 < Lp; l0 += 32) {
-    float4 a[4], r[4], p[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a[u] = pc[(l0 + 8 * u) / 4];
-      r[u] = pr[(l0 + 8 * u) / 4];
-      p[u] = pp[(l0 + 8 * u) / 4];
-    }
-    // all twelve loads of the chunk in flight before its first MFMA (the
-    // compiler would otherwise issue each step's loads after the previous
-    // step's MFMAs and wait on them one step at a time)
-    __builtin_amdgcn_sched_barrier(0);
-    v16f ac = {}, ar = {};
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      ac = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].x, p[u].x, ac, 0, 0, 0);
-      ar = __builtin_amdgcn_mfma_f32_32x32x2f32(r[u].x, fabsf(p[u].x), ar, 0, 0, 0);
-      ac = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].y, p[u].y, ac, 0, 0, 0);
-      ar = __builtin_amdgcn_mfma_f32_32x32x2f32(r[u].y, fabsf(p[u].y), ar, 0, 0, 0);
-      ac = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].z, p[u].z, ac, 0, 0, 0);
-      ar = __builtin_amdgcn_mfma_f32_32x32x2f32(r[u].z, fabsf(p[u].z), ar, 0, 0, 0);
-      ac = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u].w, p[u].w, ac, 0, 0, 0);
-      ar = __builtin_amdgcn_mfma_f32_32x32x2f32(r[u].w, fabsf(p[u].w), ar, 0, 0, 0);
-    }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      sc[e] += (double)ac[e];
-      sr[e] += (double)ar[e];
-    }
-  }
+  for (int l0 = 0; l0 < Lp; l0 += 32) k6m_chunk(pc, pr, pp, l0, sc, sr);
   // accumulator e of lane (i, h) holds box row 8 (e / 4) + 4 h + e % 4, bus column i
   if (bus >= net.Np) return;
   double* gci = ws_ptr<double>(ws, lay.gci);
@@ -928,6 +973,50 @@ __global__ __launch_bounds__(256) void k6m_ptdf_t_mfma(DevNet net, void* ws, WsL
       gci[b * net.Np + bus] = real ? sc[e] : 0.0;
       gri[b * net.Np + bus] = real ? sr[e] : 0.0;
     }
+  }
+}
+
+// The same chunks where 64 x 64 tiles give few waves: the eight waves of a block
+// share one 32 x 32 tile, wave w takes every eighth chunk of lines, and their float64
+// sums meet in LDS.  One wave walks every line otherwise (8316 buses, 4 boxes 2716 ->
+// 306 us; 2000 buses, 16 boxes 161 -> 38 us, 256 boxes 186 -> 87; 500 buses, 37 boxes
+// 40 -> 15), and fewer than eight 64-box tiles leave XCDs idle (8316 buses, 256 boxes
+// 3135 -> 1597 us).  From about 640 waves on the plain kernel's shared rows win: 500
+// buses, 2048 boxes (1024 waves) 45 against 51 us.
+constexpr int64_t kK6SplitWaves = 640;
+
+__global__ __launch_bounds__(512) void k6m_ptdf_t_split(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
+  __shared__ double sh[8][8][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = lane & 31, h = lane >> 5;
+  const int64_t box0 = (int64_t)blockIdx.y * 32;
+  const int bus = blockIdx.x * 32 + i;
+  const int Lp = net.Lp;
+  const size_t arow = (size_t)min(box0 + i, n_box - 1) * Lp + 4 * h;
+  const float4* pc = reinterpret_cast<const float4*>(ws_ptr<float>(ws, lay.gcf) + arow);
+  const float4* pr = reinterpret_cast<const float4*>(ws_ptr<float>(ws, lay.grf) + arow);
+  const float4* pp = reinterpret_cast<const float4*>(net.phiT + (size_t)min(bus, net.N - 1) * Lp + 4 * h);
+  double sc[16], sr[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) sc[e] = sr[e] = 0.0;
+  for (int l0 = 32 * w; l0 < Lp; l0 += 32 * 8) k6m_chunk(pc, pr, pp, l0, sc, sr);
+  double* gci = ws_ptr<double>(ws, lay.gci);
+  double* gri = ws_ptr<double>(ws, lay.gri);
+  const bool real = bus < net.N;
+  // eight of a lane's 32 sums at a time; wave w finishes the w-th of them
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double* v = (q < 2 ? sc : sr) + 8 * (q & 1);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sh[w][e][lane] = v[e];
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t += sh[u][w][lane];
+    const int e = 8 * (q & 1) + w;
+    const int64_t b = box0 + 8 * (e >> 2) + 4 * h + (e & 3);
+    if (b < n_box) (q < 2 ? gci : gri)[b * net.Np + bus] = real ? t : 0.0;
   }
 }
 
@@ -1006,19 +1095,26 @@ hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, co
     tm->stop(t, s);
   } else if (n_box >= kBatchMin && lay.batched && net.K > 0) {
     const int t = tm->start(7, s);
-    const unsigned groups = (unsigned)(((n_box + kBT5 - 1) / kBT5 + 3) / 4);
-    const dim3 grid(lay.k5_tiles, lay.k5_by, groups);
+    const int64_t tiles = (n_box + kBT5 - 1) / kBT5;
+    const bool split = tiles * lay.k5_tiles * lay.k5_by <= kK5SplitTiles;
+    const dim3 grid(lay.k5_tiles, lay.k5_by, (unsigned)(split ? tiles : (tiles + 3) / 4));
     const float2* cb_all = reinterpret_cast<const float2*>(static_cast<char*>(ws) + lay.cb);
     float2* cpart_all = reinterpret_cast<float2*>(static_cast<char*>(ws) + lay.cpart);
+    auto go = [&](auto mode) {
+      constexpr int M = decltype(mode)::value;
+      if (split)
+        hipLaunchKernelGGL((k5b_outage_vjp<M, true>), grid, dim3(512), 0, s, net, ws, lay, n_box, g_lo, g_hi, cb_all,
+                           cpart_all);
+      else
+        hipLaunchKernelGGL((k5b_outage_vjp<M, false>), grid, dim3(256), 0, s, net, ws, lay, n_box, g_lo, g_hi, cb_all,
+                           cpart_all);
+    };
     if (!g_lo)
-      hipLaunchKernelGGL(k5b_outage_vjp<1>, grid, dim3(256), 0, s, net, ws, lay, n_box, g_lo, g_hi, cb_all,
-                         cpart_all);
+      go(std::integral_constant<int, 1>());
     else if (!g_hi)
-      hipLaunchKernelGGL(k5b_outage_vjp<2>, grid, dim3(256), 0, s, net, ws, lay, n_box, g_lo, g_hi, cb_all,
-                         cpart_all);
+      go(std::integral_constant<int, 2>());
     else
-      hipLaunchKernelGGL(k5b_outage_vjp<3>, grid, dim3(256), 0, s, net, ws, lay, n_box, g_lo, g_hi, cb_all,
-                         cpart_all);
+      go(std::integral_constant<int, 3>());
     tm->stop(t, s);
   }
   for (int64_t b0 = 0; b0 < n_box; b0 += 65535) {
@@ -1038,8 +1134,12 @@ hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, co
     const int t = tm->start(8, s);
     if (lay.k2_mfma) {
       const int n_bt = (int)((n_box + kMB - 1) / kMB), n_nt = (net.Np + kMN - 1) / kMN;
-      hipLaunchKernelGGL(k6m_ptdf_t_mfma, dim3((unsigned)(8 * ((n_bt + 7) / 8) * n_nt)), dim3(256), 0, s, net, ws,
-                         lay, n_box, n_bt, n_nt);
+      if (n_bt <= 8 || (int64_t)n_bt * n_nt * 4 <= kK6SplitWaves)
+        hipLaunchKernelGGL(k6m_ptdf_t_split, dim3(net.Np / 32, (unsigned)((n_box + 31) / 32)), dim3(512), 0, s, net, ws,
+                           lay, n_box);
+      else
+        hipLaunchKernelGGL(k6m_ptdf_t_mfma, dim3((unsigned)(8 * ((n_bt + 7) / 8) * n_nt)), dim3(256), 0, s, net, ws,
+                           lay, n_box, n_bt, n_nt);
     } else {
       hipLaunchKernelGGL(k6b_ptdf_t_tiled, dim3((net.Np + kGN - 1) / kGN, (unsigned)((n_box + kGB - 1) / kGB)),
                          dim3(256), 0, s, net, ws, lay, n_box);

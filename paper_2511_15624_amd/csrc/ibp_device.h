@@ -44,9 +44,6 @@ struct DevNet {
   const float* phiT;        // [N x Lp] float32 PTDF transposed (row n = column n of Phi), zero padding
   const float* lodf;        // [K x Lp] float32 outage factors, NaN at (k, c(k)), zero padding
   const float* lodfT;       // [L x Kp] the same factors line-major (row l: every outage's factor on line l)
-  const int8_t* lin_dig;    // digit planes of the outage factors (linear sweep), nullptr: that sweep is off
-  const int8_t* lin_dga;    // digit planes of their magnitudes
-  const float* lin_smp;     // [Lp][64] magnitudes of 64 outages' factors per line
   const float* lam_max;     // [Lp] max over outages of |factor| on the line, rounded up (0 on padding lines)
   const double* fmax_b;     // [L]
   const double* fmax_c;     // [L]
@@ -67,8 +64,11 @@ struct DevNet {
   const double4* seg;       // [S] (slope a, shift b, cap U, |U| if finite else 0)
   double zeta_inj, zeta_f;
   double phi_err_max;
-  double fmax_c_min;        // smallest post-outage limit
   double gamma64_n;         // float64 accumulation bound for one PTDF row
+  double fmax_c_min;        // smallest post-outage limit
+  const int8_t* lin_dig;    // digit planes of the outage factors (linear sweep), nullptr: that sweep is off
+  const int8_t* lin_dga;    // digit planes of their magnitudes
+  const float* lin_smp;     // [Lp][64] magnitudes of 64 outages' factors per line
 };
 
 // Workspace carve-up for n_box boxes.  Offsets in bytes from the base pointer.
@@ -105,7 +105,6 @@ struct WsLayout {
   // screened backward sweep of the gradient of f_hi (box-tiled calls): the
   // lines that may hold an active lower-penalty element, per tile of boxes
   int k5s_tiles = 0;               // tiles of kScreenBoxes boxes (0: not laid out)
-  int rscreen = 0;                 // the upper relaxation's slopes by the screened sweep
   int fscreen = 0;                 // one-sided box-tiled forward calls take the screened sweep
   size_t smask = 0;                // uint64 [tiles][Lp / 64]: candidate-line bit masks
   size_t srec = 0;                 // float [tiles][Lp][12]: the tile's boxes' centres and radius terms
@@ -113,16 +112,6 @@ struct WsLayout {
   size_t sw = 0;                   // float [tiles][Kp]: per tile and outage, max over its boxes of max(|c_c| - r_c, 0)
   size_t sz = 0;                   // float [tiles][k5w_bx]: per tile and 256 outages, max |c_c| + r_c
   int k5w_bx = 0;                  // blocks of 256 outages (Kp / 256 rounded up)
-  // linear outage sweep of box-tiled calls (see ibp_linear.hip), in the memory
-  // of the base-flow partials, which are dead after the line epilogue
-  int lin = 0;                     // 1: that sweep (p3 then lies in that memory too)
-  size_t oc = 0;                   // float2 [groups][K][64]: (c_c, rho'_k) of a group's boxes
-  size_t ow = 0;                   // float [groups][Kp]: the group's max |c_c| + rho'_k
-  size_t hq = 0;                   // uint64 [groups][Lp / 4]: boxes whose flow on a line of the quad is heavy
-  size_t nk = 0;                   // uint64 [groups][Lp]: boxes of the group whose flow on the line is near a kink
-  size_t vu = 0, vl = 0;           // int8 [2 groups][Lp / 32][64][16]: sign where the base penalty is active
-  size_t pe = 0;                   // double2 [B][n_pe]: sums of absolute terms (hi, lo)
-  int n_pe = 0, lin_lb = 0;        // partials per box; line blocks
   // linear-relaxation bound (present with the CROWN flag)
   size_t ccnt = 0;                 // int2 [B][Lp]: per-line (sum s, sum |s|) over outages
   size_t cv = 0;                   // double4 [B][kc_bx][K]: per-outage (sum s Lam, sum |s Lam|, count)
@@ -141,6 +130,17 @@ struct WsLayout {
   size_t fwd_total = 0;            // bytes of the forward arrays above (inj .. p3)
   size_t ref = 0;                  // a second forward region, for the reference points
   size_t xref = 0, vtx = 0;        // float [B][X]: reference points, maximising vertices
+  int rscreen = 0;                 // the upper relaxation's slopes by the screened sweep
+  // linear outage sweep of box-tiled calls (see ibp_linear.hip), in the memory
+  // of the base-flow partials, which are dead after the line epilogue
+  int lin = 0;                     // 1: that sweep (p3 then lies in that memory too)
+  size_t oc = 0;                   // float2 [groups][K][64]: (c_c, rho'_k) of a group's boxes
+  size_t ow = 0;                   // float [groups][Kp]: the group's max |c_c| + rho'_k
+  size_t hq = 0;                   // uint64 [groups][Lp / 4]: boxes whose flow on a line of the quad is heavy
+  size_t nk = 0;                   // uint64 [groups][Lp]: boxes of the group whose flow on the line is near a kink
+  size_t vu = 0, vl = 0;           // int8 [2 groups][Lp / 32][64][16]: sign where the base penalty is active
+  size_t pe = 0;                   // double2 [B][n_pe]: sums of absolute terms (hi, lo)
+  int n_pe = 0, lin_lb = 0;        // partials per box; line blocks
 };
 
 }  // namespace ibp
