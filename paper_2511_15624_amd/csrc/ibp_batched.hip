@@ -28,7 +28,7 @@ namespace ibp {
 constexpr int kBT = 4;  // boxes per wave tile of the vector base-flow sweep (and the outage sweep's default)
 
 // Base flows for kBT boxes x 256 lines per wave, over every bus.
-__global__ __launch_bounds__(256) void k2b_base_flows(DevNet net, void* ws, WsLayout lay, int64_t n_box,
+__global__ __launch_bounds__(256) void k2b_base_flows(DevNet net, void* ws, FwdLayout lay, int64_t n_box,
                                                       const double2* __restrict__ inj_all) {
   const int Lp4 = net.Lp / 4;
   if ((int)blockIdx.x * 64 >= Lp4) return;  // padding block of the grid
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void k2b_base_flows(DevNet net, void* ws, WsLa
 // the same accumulation bound as the vector kernels).
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256, 2) void k2b_base_flows_mfma(DevNet net, void* ws, WsLayout lay, int64_t n_box,
+__global__ __launch_bounds__(256, 2) void k2b_base_flows_mfma(DevNet net, void* ws, FwdLayout lay, int64_t n_box,
                                                               const double2* __restrict__ inj_all) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
@@ -189,7 +189,7 @@ constexpr int kThinBuses = 32;  // buses of a stage: a phi quad and an injection
 constexpr int kThinRow = 64 + 16;  // floats of a phi row in LDS: a wave's four rows meet all 64 banks
 constexpr int64_t kThinBlocks = 2560;
 
-__global__ __launch_bounds__(512) void k2b_base_flows_thin(DevNet net, void* ws, WsLayout lay, int64_t n_box,
+__global__ __launch_bounds__(512) void k2b_base_flows_thin(DevNet net, void* ws, FwdLayout lay, int64_t n_box,
                                                            const double2* __restrict__ inj_all) {
   __shared__ float4 sp[2][kThinBuses * kThinRow / 4];
   __shared__ double sc[2][2][kThinBuses * 16];
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(512) void k2b_base_flows_thin(DevNet net, void* ws,
 // the last-level cache the plain order is faster (2000 buses: 27.3 against
 // 28.4 ms).  The order changes no sum.
 template <int SIDES, int kBT>
-__global__ __launch_bounds__(256) void k3b_contingency(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
+__global__ __launch_bounds__(256) void k3b_contingency(DevNet net, void* ws, FwdLayout lay, int64_t n_box) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;

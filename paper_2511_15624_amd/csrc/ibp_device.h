@@ -72,7 +72,11 @@ struct DevNet {
 };
 
 // Workspace carve-up for n_box boxes.  Offsets in bytes from the base pointer.
-struct WsLayout {
+//
+// A launch copies its arguments to memory that the kernel's first reads come to cold, so
+// the forward kernels take the part they read and not the whole (840 bytes of
+// arguments otherwise, 500 so).
+struct FwdLayout {
   size_t inj = 0;                  // double2 [B][Np]: (c32, r'') of the injections, as float64
   size_t p1 = 0;                   // double [B][n_p1][kP1Fields]: box-preparation partial sums
   size_t part2 = 0;                // double2 [B][n_by][Lp]: base-flow partial sums (centre, radius)
@@ -82,23 +86,28 @@ struct WsLayout {
   size_t ctg = 0;                  // int4 [B][K]: (line, centre bits, rho' bits, unpadded radius bits)
   size_t p2 = 0;                   // double2 [B][n_p2]: base-penalty partial sums (hi, lo)
   size_t p3 = 0;                   // double2 [B][n_p3]: contingency partial sums (hi, lo)
+  size_t cb = 0;                   // float2 [B][K]: backward per-outage (centre, unpadded radius); 0: absent
+  int n_p1 = 0, n_p2 = 0, n_p3 = 0;
+  int k2_by = 0;                   // bus chunks of the base flows (K2 grid per box: line tiles x bus chunks)
+  int k2_chunk = 0;                // batched base flows: buses per chunk (k2_by chunks, a multiple of 4)
+  int k3_kper = 0;                 // batched outage sweep: outages per block row
+  int k3_xcd = 0;                  // box-tiled outage sweep in XCD-aware block order
+  int sides = 3;                   // penalty sides of the outage sweep: 3 both, 1 lower (f_hi), 2 upper (f_lo)
+};
+
+struct WsLayout : FwdLayout {
   size_t lpart = 0;                // float2 [B][k5_by][Lp]: backward per-line partials (d centre, d radius)
   size_t cpart = 0;                // float2 [B][k5_tiles][K]: backward per-outage partials
   size_t gcf = 0, grf = 0;         // float [B][Lp]: backward line gradients (centre, radius)
   size_t gci = 0, gri = 0;         // double [B][Np]: backward injection gradients
-  size_t cb = 0;                   // float2 [B][K]: backward per-outage (centre, unpadded radius); 0: absent
   size_t total = 0;
-  int n_p1 = 0, n_p2 = 0, n_p3 = 0;
-  int k2_bx = 0, k2_by = 0;        // K2 grid per box (line tiles x bus chunks)
+  int k2_bx = 0;                   // K2 line tiles per box
   int k3_bx = 0, k3_by = 0;        // K3 grid per box (line tiles x outage chunks)
   int k2_nc = 0, k3_kc = 0;        // tile parameters used
   int batched = 0;                 // 1: box-tiled kernels (boxes share every streamed tile)
   int small = 0;                   // 1: smallest networks, one launch and one block per box (km_box)
-  int sides = 3;                   // penalty sides of the outage sweep: 3 both, 1 lower (f_hi), 2 upper (f_lo)
   int k2_gx = 0;                   // batched base flows: grid x (line tiles padded to a multiple of 8)
   int k2_mfma = 0;                 // batched base flows on the float64 matrix cores
-  int k2_chunk = 0;                // batched base flows: buses per chunk (k2_by chunks, a multiple of 4)
-  int k3_kper = 0;                 // batched outage sweep: outages per block row
   int k3_bt = 4;                   // batched outage sweep: boxes per wave
   int k5_by = 0, k5_tiles = 0;     // backward outage sweep: outage chunks, line tiles
   int k5_chunk = 0;                // outages per backward chunk
@@ -122,7 +131,6 @@ struct WsLayout {
   size_t ct = 0;                   // double2 [B][n_ct]: per-line partial sums (limit total, sum vabs)
   int kc_bx = 0, kc_by = 0, kc3_bx = 0, kc3_by = 0, n_cp = 0, n_ct = 0;
   int chord_nb = 1;                // boxes per lane of the box-tiled chord sweep
-  int k3_xcd = 0;                  // box-tiled outage sweep in XCD-aware block order
   size_t chp = 0;                  // int2 [B][chp_z][Lp]: per-box chord sweep, per-block line totals
   int chp_z = 0;                   // outage blocks of the per-box chord sweep (0: box-tiled, atomics)
   int kc3_mfma = 0, kc3_chunk = 0; // box-tiled transposed PTDF on the matrix cores: lines per chunk (kc3_bx chunks)
@@ -142,5 +150,19 @@ struct WsLayout {
   size_t pe = 0;                   // double2 [B][n_pe]: sums of absolute terms (hi, lo)
   int n_pe = 0, lin_lb = 0;        // partials per box; line blocks
 };
+
+// Reads one word of each 64-byte line of the kernel's arguments.  A kernel that comes
+// to its arguments piece by piece waits for each new line (the launch wrote them to
+// memory); these reads wait for all of them at once.
+template <int BYTES>
+__device__ __forceinline__ void touch_args() {
+  typedef const __attribute__((address_space(4))) unsigned* Args;
+  const Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+  unsigned x[BYTES / 64];
+#pragma unroll
+  for (int i = 0; i < BYTES / 64; ++i) x[i] = p[16 * i];
+#pragma unroll
+  for (int i = 0; i < BYTES / 64; ++i) asm volatile("" ::"s"(x[i]));
+}
 
 }  // namespace ibp

@@ -108,7 +108,7 @@ __device__ __forceinline__ void input_terms(const DevNet& net, int i, double l, 
 
 // Neutral padding lines for K3 (zero centre, h = -FLT_MAX, g = +FLT_MAX) and
 // the box's Vmax slot cleared; run by one block per box.
-__device__ __forceinline__ void box_slots_init(const DevNet& net, void* ws, const WsLayout& lay, int64_t b) {
+__device__ __forceinline__ void box_slots_init(const DevNet& net, void* ws, const FwdLayout& lay, int64_t b) {
   float* lc = ws_ptr<float>(ws, lay.lc) + b * net.Lp;
   float* lh = ws_ptr<float>(ws, lay.lh) + b * net.Lp;
   float* lg = ws_ptr<float>(ws, lay.lg) + b * net.Lp;
@@ -125,7 +125,7 @@ __device__ __forceinline__ void box_slots_init(const DevNet& net, void* ws, cons
 // total injection and the padding constants.
 __global__ __launch_bounds__(64) void k1_box_prep(DevNet net, const float* __restrict__ box_lo,
                                                   const float* __restrict__ box_hi, void* ws,
-                                                  WsLayout lay, int64_t box0) {
+                                                  FwdLayout lay, int64_t box0) {
   const int64_t b = box0 + blockIdx.y;
   const int i = blockIdx.x * 64 + threadIdx.x;
   const float* lo = box_lo + b * net.X;
@@ -227,7 +227,7 @@ constexpr int kK2eBy = 16;  // base-flow partials per line loaded in one round
 // clamped; partials that do not exist are skipped by wave-uniform or lane
 // masks, not loaded twice), so the kernel waits on memory about twice
 // instead of once per dependent step.
-__global__ __launch_bounds__(kK2eThreads) void k2e_lines(DevNet net, void* ws, WsLayout lay, int64_t box0) {
+__global__ __launch_bounds__(kK2eThreads) void k2e_lines(DevNet net, void* ws, FwdLayout lay, int64_t box0) {
   const int64_t b = box0 + blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kK2eThreads) void k2e_lines(DevNet net, void* ws, W
 // share the line tile; their sums are combined in LDS and written as one
 // partial per block row (bus chunk).
 template <int NC>
-__global__ __launch_bounds__(256) void k2_base_flows(DevNet net, void* ws, WsLayout lay, int64_t box0,
+__global__ __launch_bounds__(256) void k2_base_flows(DevNet net, void* ws, FwdLayout lay, int64_t box0,
                                                      const double2* __restrict__ inj_all) {
   __shared__ double sh[3][64][8];
   const int64_t b = box0 + blockIdx.z;
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256) void k2_base_flows(DevNet net, void* ws, WsLay
 
 // ---------------------------------------------------------------- K4
 
-__device__ __forceinline__ void objective_interval(const DevNet& net, const WsLayout& lay, int64_t b,
+__device__ __forceinline__ void objective_interval(const DevNet& net, const FwdLayout& lay, int64_t b,
                                                    const double (&x)[12], double* __restrict__ f_lo,
                                                    double* __restrict__ f_hi, double* __restrict__ terms,
                                                    double pad_hi = 0.0, double pad_lo = 0.0);
@@ -391,7 +391,8 @@ __device__ __forceinline__ void objective_interval(const DevNet& net, const WsLa
 // threads after every partial is visible.  The first T partials of each kind
 // are loaded in one group (clamped indices, masked adds); loops take the rest.
 template <int T, bool LIN>
-__device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, int64_t b,
+__device__ void finalize_box(const DevNet& net, void* ws, const std::conditional_t<LIN, WsLayout, FwdLayout>& lay,
+                             int64_t b,
                              double* __restrict__ f_lo, double* __restrict__ f_hi,
                              double* __restrict__ terms) {
   const double* p1 = ws_ptr<double>(ws, lay.p1) + b * lay.n_p1 * kP1Fields;
@@ -454,7 +455,7 @@ __device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, i
   if ((tid & 63) == 0)
 #pragma unroll
     for (int f = 0; f < 12; ++f) red[tid >> 6][f] = x[f];
-  if (LIN) {
+  if constexpr (LIN) {
     const double2* pe = ws_ptr<double2>(ws, lay.pe) + b * lay.n_pe;
     double eh = 0.0, el = 0.0;
     for (int i = tid; i < lay.n_pe; i += T) {
@@ -482,7 +483,7 @@ __device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, i
 #pragma unroll
   for (int f = 0; f < 12; ++f) x[f] = tot[f];
   double pad_hi = 0.0, pad_lo = 0.0;
-  if (LIN) {
+  if constexpr (LIN) {
     // what the linear sweep's float64 sums (absolute terms eh, el; their
     // exceptions add at most twice those) and its 2^-38 factors may be off,
     // beyond the part of the totals' float32 allowance that it does not use
@@ -510,7 +511,7 @@ __device__ void finalize_box(const DevNet& net, void* ws, const WsLayout& lay, i
 // preparation fields from kP1Sc on (surplus centre, radius and magnitude,
 // total injection centre, radius and magnitude, invalid count), x[8], x[9]
 // the base penalties (hi, lo), x[10], x[11] the outage penalties (hi, lo).
-__device__ __forceinline__ void objective_interval(const DevNet& net, const WsLayout& lay, int64_t b,
+__device__ __forceinline__ void objective_interval(const DevNet& net, const FwdLayout& lay, int64_t b,
                                                    const double (&x)[12], double* __restrict__ f_lo,
                                                    double* __restrict__ f_hi, double* __restrict__ terms,
                                                    double pad_hi, double pad_lo) {
@@ -565,7 +566,8 @@ __device__ __forceinline__ void objective_interval(const DevNet& net, const WsLa
 
 // One block of T threads per box.
 template <int T, bool LIN>
-__global__ __launch_bounds__(T) void k4_finalize(DevNet net, void* ws, WsLayout lay, int64_t box0,
+__global__ __launch_bounds__(T) void k4_finalize(DevNet net, void* ws,
+                                                 std::conditional_t<LIN, WsLayout, FwdLayout> lay, int64_t box0,
                                                  double* __restrict__ f_lo, double* __restrict__ f_hi,
                                                  double* __restrict__ terms) {
   finalize_box<T, LIN>(net, ws, lay, box0 + blockIdx.x, f_lo, f_hi, terms);
@@ -603,7 +605,7 @@ static void launch_k4(const DevNet& net, void* ws, const WsLayout& lay, int64_t 
 // padding of the box's vmax; returns the block's penalty sums (hi, lo) in
 // thread 0.
 template <int KC>
-__device__ __forceinline__ double2 k3_block(const DevNet& net, void* ws, const WsLayout& lay, int64_t b, int col,
+__device__ __forceinline__ double2 k3_block(const DevNet& net, void* ws, const FwdLayout& lay, int64_t b, int col,
                                             int k0, int k1, float vmax) {
   __shared__ double sh[8];
   const int lane = threadIdx.x & 63;
@@ -658,7 +660,7 @@ __device__ __forceinline__ double2 k3_block(const DevNet& net, void* ws, const W
 }
 
 template <int KC>
-__global__ __launch_bounds__(256) void k3_contingency(DevNet net, void* ws, WsLayout lay, int64_t box0) {
+__global__ __launch_bounds__(256) void k3_contingency(DevNet net, void* ws, FwdLayout lay, int64_t box0) {
   const int64_t b = box0 + blockIdx.z;
   const int col = (blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * 64 + (int)(threadIdx.x & 63);  // float4 column
   const double* bs = ws_ptr<double>(ws, lay.box) + b * kBoxSlots;
@@ -682,22 +684,72 @@ __global__ __launch_bounds__(256) void k3_contingency(DevNet net, void* ws, WsLa
 // float32 penalty sums have the same depth), so the padding is unchanged.
 // Every load that does not depend on another is issued before the first use.
 // SWEEP = false stops after the line epilogue (the backward's preparation).
+//
+// T = 256 threads for the smallest, T = 1024 from kMicroWideElems PTDF and factor
+// elements on: one block's time is its loads' latencies in a row (sixteen buses of a
+// column at a time, one item of the sweep at a time), so a wide block stages the
+// PTDF in LDS, a line per thread, and has the sweep's first items loaded from the
+// start.  One box, whole call: 57 buses 16.2 -> 13.7 us (the host's share), 107
+// buses 26.2 -> 16.4, 160 buses 39.8 -> 23.3; at 39 buses both are the host's 13.5.
+// The sums over buses keep their order.
 constexpr int kMicroBuses = 256;
 constexpr int kMicroLines = 1024;
 constexpr int kMicroElems = 65536;
 
-template <bool SWEEP>
-__global__ __launch_bounds__(256) void km_box(DevNet net, const float* __restrict__ box_lo,
-                                              const float* __restrict__ box_hi, void* ws, WsLayout lay, int64_t box0,
+constexpr int kMicroStage = 16384;  // floats of PTDF rows that a wide block stages in LDS
+constexpr int64_t kMicroWideElems = 8192;
+
+static bool micro_wide(const DevNet& net) { return (int64_t)(net.K + net.N) * net.Lp > kMicroWideElems; }
+
+template <int T, bool SWEEP>
+__global__ __launch_bounds__(T) void km_box(DevNet net, const float* __restrict__ box_lo,
+                                              const float* __restrict__ box_hi, void* ws, FwdLayout lay, int64_t box0,
                                               double* __restrict__ f_lo, double* __restrict__ f_hi,
                                               double* __restrict__ terms) {
   __shared__ double2 inj[kMicroBuses];
   __shared__ float s_lc[kMicroLines], s_lh[kMicroLines], s_lg[kMicroLines];
   __shared__ int4 s_ctg[kMicroElems / 64];
-  __shared__ double red[4][kP1Fields + 4];
-  __shared__ unsigned redm[4];
+  constexpr int W = T / 64;
+  constexpr bool WIDE = T > 256;
+  __shared__ alignas(16) float stage[WIDE ? kMicroStage : 1];
+  __shared__ double red[W][kP1Fields + 4];
+  __shared__ unsigned redm[W];
   const int64_t b = box0 + blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  touch_args<sizeof(DevNet) + sizeof(FwdLayout)>();
+  // operands that depend on nothing: the first PTDF rows and outage factors
+  const int Lp4 = net.Lp / 4;
+  const int rows = WIDE ? kMicroStage / net.Lp : 0;  // PTDF rows staged at a time
+  constexpr int kStageQ = WIDE ? kMicroStage / 4 / T : 1;
+  static_assert(!WIDE || kStageQ == 4, "four quads of the staged rows per thread");
+  typedef float v4f __attribute__((ext_vector_type(4)));
+  v4f p0, p1, p2, p3;
+  auto load_rows = [&](int n0) {
+    const int nq = min(rows, net.N - n0) * Lp4;
+    const v4f* p = reinterpret_cast<const v4f*>(net.phiT) + (size_t)n0 * Lp4;
+    p0 = p[min(tid, nq - 1)];
+    p1 = p[min(tid + T, nq - 1)];
+    p2 = p[min(tid + 2 * T, nq - 1)];
+    p3 = p[min(tid + 3 * T, nq - 1)];
+  };
+  if constexpr (WIDE) load_rows(0);
+  // outage sweep: items (column of four lines, pair of outages), columns fastest
+  const int np = SWEEP ? net.K / 2 : 0;
+  const float4* lam = reinterpret_cast<const float4*>(net.lodf);
+  constexpr int kAhead = 2;
+  float4 xa[kAhead], xb[kAhead];
+  auto load_items = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int it = i0 + u * T;
+      if (it < np * Lp4) {
+        const int col = it % Lp4, k = 2 * (it / Lp4);
+        xa[u] = lam[(size_t)k * Lp4 + col];
+        xb[u] = lam[(size_t)(k + 1) * Lp4 + col];
+      }
+    }
+  };
+  if (WIDE && SWEEP) load_items(tid);
   const float* lo = box_lo + b * net.X;
   const float* hi = box_hi + b * net.X;
   // line constants of this thread's first line, loaded with the box
@@ -706,51 +758,86 @@ __global__ __launch_bounds__(256) void km_box(DevNet net, const float* __restric
   double v[kP1Fields];
 #pragma unroll
   for (int f = 0; f < kP1Fields; ++f) v[f] = 0.0;
-  if (tid < net.N) {
+  if (tid < net.N) {  // at most kMicroBuses
     double2 cr;
     bus_injection(net, lo, hi, tid, cr, v[kP1Mc], v[kP1Mbox]);
     inj[tid] = cr;
   }
-  for (int i = tid; i < net.X; i += 256) input_terms(net, i, lo[i], hi[i], net.dev_w[i], v);
+  if (!WIDE || tid < 256)
+    for (int i = tid; i < net.X; i += 256) input_terms(net, i, lo[i], hi[i], net.dev_w[i], v);
   box_slots_init(net, ws, lay, b);
-  for (int l = net.L + tid; l < net.Lp; l += 256) {
+  for (int l = net.L + tid; l < net.Lp; l += T) {
     s_lc[l] = 0.0f;
     s_lh[l] = -FLT_MAX;
     s_lg[l] = FLT_MAX;
   }
+  if (!WIDE || w < 4) {  // the other waves of a wide block hold no bus and no input
 #pragma unroll
-  for (int f = 0; f < kP1Fields; ++f) v[f] = wave_sum(v[f]);
-  if (lane == 0)
+    for (int f = 0; f < kP1Fields; ++f) v[f] = wave_sum(v[f]);
+    if (lane == 0)
 #pragma unroll
-    for (int f = 0; f < kP1Fields; ++f) red[w][f] = v[f];
+      for (int f = 0; f < kP1Fields; ++f) red[w][f] = v[f];
+  }
   __syncthreads();
 #pragma unroll
   for (int f = 0; f < kP1Fields; ++f) v[f] = (red[0][f] + red[1][f]) + (red[2][f] + red[3][f]);
-  if (tid < kP1Fields) ws_ptr<double>(ws, lay.p1)[b * kP1Fields + tid] = v[tid];
+  if (tid < kP1Fields)
+    ws_ptr<double>(ws, lay.p1)[b * kP1Fields + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
   const double g = (net.N + 64) * kU64 * 1.01;
   const double mc = v[kP1Mc] * (1.0 + g), mb = v[kP1Mbox] * (1.0 + g);
 
-  // base flows (sixteen PTDF loads in flight per step) and the line epilogue
+  // base flows and the line epilogue
   double pb_hi = 0.0, pb_lo = 0.0;
   unsigned vm = 0u;
-  for (int l = tid; l < net.L; l += 256) {
-    double cf = 0.0, rh = 0.0;
-    for (int n0 = 0; n0 < net.N; n0 += 16) {
-      float x[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = n0 + u < net.N ? net.phiT[(size_t)(n0 + u) * net.Lp + l] : 0.0f;
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (n0 + u < net.N) {
-          const double2 cr = inj[n0 + u];
-          cf = fma((double)x[u], cr.x, cf);
-          rh = fma(fabs((double)x[u]), cr.y, rh);
-        }
-    }
+  auto epilogue = [&](int l, double cf, double rh) {
     const LineConst q = l == l0 ? q0 : load_line_const(net, l);
     vm = max(vm, line_epilogue(net, l, q, cf, rh, mc, mb, s_lc, s_lh, s_lg, ws_ptr<double>(ws, lay.lcf) + b * net.L,
                                ws_ptr<double>(ws, lay.lrf) + b * net.L, s_ctg,
                                lay.cb ? ws_ptr<float2>(ws, lay.cb) + b * net.K : nullptr, pb_hi, pb_lo));
+  };
+  if constexpr (WIDE) {
+    // one line per thread (kMicroLines threads), its PTDF column from the staged rows
+    static_assert(T >= kMicroLines, "one line per thread");
+    double cf = 0.0, rh = 0.0;
+    for (int n0 = 0; n0 < net.N; n0 += rows) {
+      const int nr = min(rows, net.N - n0);
+      if (n0 > 0) __syncthreads();
+      v4f* st = reinterpret_cast<v4f*>(stage) + tid;  // quads past the last row fill unread words
+      st[0] = p0;
+      st[T] = p1;
+      st[2 * T] = p2;
+      st[3 * T] = p3;
+      __syncthreads();
+      if (n0 + rows < net.N) load_rows(n0 + rows);
+      if (tid < net.L) {
+#pragma unroll 8
+        for (int n = 0; n < nr; ++n) {
+          const float x = stage[n * net.Lp + tid];
+          const double2 cr = inj[n0 + n];
+          cf = fma((double)x, cr.x, cf);
+          rh = fma(fabs((double)x), cr.y, rh);
+        }
+      }
+    }
+    if (tid < net.L) epilogue(tid, cf, rh);
+  } else {
+    // sixteen PTDF loads in flight per step
+    for (int l = tid; l < net.L; l += T) {
+      double cf = 0.0, rh = 0.0;
+      for (int n0 = 0; n0 < net.N; n0 += 16) {
+        float x[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = n0 + u < net.N ? net.phiT[(size_t)(n0 + u) * net.Lp + l] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          if (n0 + u < net.N) {
+            const double2 cr = inj[n0 + u];
+            cf = fma((double)x[u], cr.x, cf);
+            rh = fma(fabs((double)x[u]), cr.y, rh);
+          }
+      }
+      epilogue(l, cf, rh);
+    }
   }
   vm = wave_max_u32(vm);
   pb_hi = wave_sum(pb_hi);
@@ -761,27 +848,25 @@ __global__ __launch_bounds__(256) void km_box(DevNet net, const float* __restric
     redm[w] = vm;
   }
   __syncthreads();
-  const unsigned vmb = max(max(redm[0], redm[1]), max(redm[2], redm[3]));
+  unsigned vmb = 0u;
+#pragma unroll
+  for (int q = 0; q < W; ++q) vmb = max(vmb, redm[q]);
   const float vmax = __uint_as_float(vmb);
   // the per-line and per-outage data for the kernels that run after this one
   float* wlc = ws_ptr<float>(ws, lay.lc) + b * net.Lp;
   float* wlh = ws_ptr<float>(ws, lay.lh) + b * net.Lp;
   float* wlg = ws_ptr<float>(ws, lay.lg) + b * net.Lp;
-  for (int l = tid; l < net.L; l += 256) {
+  for (int l = tid; l < net.L; l += T) {
     wlc[l] = s_lc[l];
     wlh[l] = s_lh[l];
     wlg[l] = s_lg[l];
   }
   int4* wctg = ws_ptr<int4>(ws, lay.ctg) + b * net.K;
-  for (int k = tid; k < net.K; k += 256) wctg[k] = s_ctg[k];
+  for (int k = tid; k < net.K; k += T) wctg[k] = s_ctg[k];
   if (tid == 0) *reinterpret_cast<unsigned*>(ws_ptr<double>(ws, lay.box) + b * kBoxSlots + kVmax) = vmb;
   if (!SWEEP) return;
 
-  // outage sweep: items (column of four lines, pair of outages), columns fastest
-  const int Lp4 = net.Lp / 4;
-  const int np = net.K / 2;
   double acc_hi = 0.0, acc_lo = 0.0;
-  const float4* lam = reinterpret_cast<const float4*>(net.lodf);
   auto column = [&](int col, float4& c4, float4& h4, float4& g4) {
     const float4 e4 = reinterpret_cast<const float4*>(net.line_eps)[col];
     c4 = make_float4(s_lc[4 * col], s_lc[4 * col + 1], s_lc[4 * col + 2], s_lc[4 * col + 3]);
@@ -790,16 +875,34 @@ __global__ __launch_bounds__(256) void km_box(DevNet net, const float* __restric
     g4 = make_float4(add_ru(s_lg[4 * col], next_up_f32(e4.x * vmax)), add_ru(s_lg[4 * col + 1], next_up_f32(e4.y * vmax)),
                      add_ru(s_lg[4 * col + 2], next_up_f32(e4.z * vmax)), add_ru(s_lg[4 * col + 3], next_up_f32(e4.w * vmax)));
   };
-  for (int it = tid; it < np * Lp4; it += 256) {
+  auto item = [&](int it, const float4& x0, const float4& x1) {
     const int col = it % Lp4, k = 2 * (it / Lp4);
-    const float4 x0 = lam[(size_t)k * Lp4 + col], x1 = lam[(size_t)(k + 1) * Lp4 + col];
     float4 c4, h4, g4;
     column(col, c4, h4, g4);
     k3_pair(x0, s_ctg[k], x1, s_ctg[k + 1], c4, h4, g4, acc_hi, acc_lo);
+  };
+  if constexpr (WIDE) {
+    for (int i0 = tid; i0 < np * Lp4; i0 += kAhead * T) {
+      float4 x0[kAhead], x1[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        x0[u] = xa[u];
+        x1[u] = xb[u];
+      }
+      load_items(i0 + kAhead * T);
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (i0 + u * T < np * Lp4) item(i0 + u * T, x0[u], x1[u]);
+    }
+  } else {
+    for (int it = tid; it < np * Lp4; it += T) {
+      const int col = it % Lp4, k = 2 * (it / Lp4);
+      item(it, lam[(size_t)k * Lp4 + col], lam[(size_t)(k + 1) * Lp4 + col]);
+    }
   }
   if (net.K & 1) {  // the last outage of an odd count, alone
     const int k = net.K - 1;
-    for (int col = tid; col < Lp4; col += 256) {
+    for (int col = tid; col < Lp4; col += T) {
       const float4 x0 = lam[(size_t)k * Lp4 + col];
       float4 c4, h4, g4;
       column(col, c4, h4, g4);
@@ -825,8 +928,16 @@ __global__ __launch_bounds__(256) void km_box(DevNet net, const float* __restric
 #pragma unroll
   for (int f = 0; f < 8; ++f) x[f] = v[kP1Sc + f];
 #pragma unroll
-  for (int f = 0; f < 4; ++f)
-    x[8 + f] = (red[0][kP1Fields + f] + red[1][kP1Fields + f]) + (red[2][kP1Fields + f] + red[3][kP1Fields + f]);
+  for (int f = 0; f < 2; ++f) {
+    double t = 0.0, u = 0.0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+      t += red[q][kP1Fields + f];
+      u += red[q][kP1Fields + 2 + f];
+    }
+    x[8 + f] = t;
+    x[10 + f] = u;
+  }
   objective_interval(net, lay, b, x, f_lo, f_hi, terms);
 }
 
@@ -882,7 +993,10 @@ hipError_t launch_forward_single(const DevNet& net, int64_t n_box, const float* 
   if (lay.small) {
     for (int64_t b0 = 0; b0 < n_box; b0 += 65535) {
       const int nb = (int)std::min<int64_t>(65535, n_box - b0);
-      tm->launch(2, km_box<true>, dim3(nb), dim3(256), s, net, lo, hi, ws, lay, b0, f_lo, f_hi, terms);
+      if (micro_wide(net))
+        tm->launch(2, km_box<1024, true>, dim3(nb), dim3(1024), s, net, lo, hi, ws, lay, b0, f_lo, f_hi, terms);
+      else
+        tm->launch(2, km_box<256, true>, dim3(nb), dim3(256), s, net, lo, hi, ws, lay, b0, f_lo, f_hi, terms);
     }
     return hipGetLastError();
   }
@@ -917,8 +1031,12 @@ hipError_t launch_forward_prep(const DevNet& net, int64_t n_box, const float* lo
     for (int64_t b0 = 0; b0 < n_box; b0 += 65535) {
       const int nb = (int)std::min<int64_t>(65535, n_box - b0);
       const int t = tm->start(0, s);
-      hipLaunchKernelGGL(km_box<false>, dim3(nb), dim3(256), 0, s, net, lo, hi, ws, lay, b0, nullptr, nullptr,
-                         nullptr);
+      if (micro_wide(net))
+        hipLaunchKernelGGL((km_box<1024, false>), dim3(nb), dim3(1024), 0, s, net, lo, hi, ws, lay, b0, nullptr,
+                           nullptr, nullptr);
+      else
+        hipLaunchKernelGGL((km_box<256, false>), dim3(nb), dim3(256), 0, s, net, lo, hi, ws, lay, b0, nullptr, nullptr,
+                           nullptr);
       tm->stop(t, s);
     }
     return hipGetLastError();
