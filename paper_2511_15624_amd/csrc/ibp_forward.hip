@@ -398,7 +398,7 @@ __device__ void finalize_box(const DevNet& net, void* ws, const std::conditional
   const double* p1 = ws_ptr<double>(ws, lay.p1) + b * lay.n_p1 * kP1Fields;
   const double2* p2 = ws_ptr<double2>(ws, lay.p2) + b * lay.n_p2;
   const double2* p3 = ws_ptr<double2>(ws, lay.p3) + b * lay.n_p3;
-  constexpr int kQ3 = 32;  // outage-sweep partials per thread in the first group
+  constexpr int kQ3 = T == 64 ? 8 : 32;  // outage-sweep partials per thread in the first group
   const int tid = threadIdx.x;
   double v[kP1Fields];
   double bh = 0, bl = 0;
@@ -575,10 +575,20 @@ __global__ __launch_bounds__(T) void k4_finalize(DevNet net, void* ws,
 
 static void launch_k4(const DevNet& net, void* ws, const WsLayout& lay, int64_t b0, int nb, double* f_lo,
                       double* f_hi, double* terms, hipStream_t s) {
-  if (lay.lin)
+  // A wave per box where one group of loads takes its outage partials (512; 500
+  // buses, 37 boxes 8.1 -> 6.2 us), and for many boxes, where the sums over the lanes are
+  // the work (14160 boxes at 20 buses 150 -> 14 us, 18432 at 2000 buses 200 -> 43).
+  // Otherwise four waves have more loads in flight (8316 buses, 256 boxes 12 against 26).
+  if (lay.n_p3 <= 512 || nb >= 1024) {
+    if (lay.lin)
+      hipLaunchKernelGGL((k4_finalize<64, true>), dim3(nb), dim3(64), 0, s, net, ws, lay, b0, f_lo, f_hi, terms);
+    else
+      hipLaunchKernelGGL((k4_finalize<64, false>), dim3(nb), dim3(64), 0, s, net, ws, lay, b0, f_lo, f_hi, terms);
+  } else if (lay.lin) {
     hipLaunchKernelGGL((k4_finalize<256, true>), dim3(nb), dim3(256), 0, s, net, ws, lay, b0, f_lo, f_hi, terms);
-  else
+  } else {
     hipLaunchKernelGGL((k4_finalize<256, false>), dim3(nb), dim3(256), 0, s, net, ws, lay, b0, f_lo, f_hi, terms);
+  }
 }
 
 // ---------------------------------------------------------------- K3

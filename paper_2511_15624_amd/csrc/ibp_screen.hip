@@ -43,19 +43,24 @@ namespace ibp {
 
 constexpr int kScreenChunk = 128;  // outages per LDS chunk of the screen
 
-// Tiles per screen block (they share every factor load), and the outage ranges a
-// line block and tile group is split over when those alone leave the chip idle:
-// partial maxima then meet in the first word of the tile's line record, and
-// k5s_mark takes the marks from there.  About kScreenBlocks blocks (2000 buses:
-// 8 boxes 600 -> 30 us, 1024 boxes 0.42 -> 0.21 ms; from 4096 boxes on, 0.72 ms, no
-// split is needed).
+// Tiles per screen block: sixteen share every factor load where outages are many (1024
+// boxes at 2000 buses, with the split below 0.21 ms; four and no split 0.42) or
+// blocks too; with few outages the marks are the work, and four finish earlier (2533 boxes
+// at 529 buses 79 against 96 us, 14160 at 20 buses 12 against 33).
+//
+// Outage ranges a line block and tile group is split over when those alone leave the
+// chip idle (below 384 blocks): partial maxima then meet in the first word of the tile's
+// line record, and k5s_mark takes the marks from there.  About kScreenBlocks blocks
+// (2000 buses, 8 boxes: 600 -> 30 us).
 constexpr int kScreenBlocks = 1024;
 inline int screen_tiles(const DevNet& net, const WsLayout& lay) {
-  return ((int64_t)lay.k5s_tiles + 15) / 16 * ((net.Lp + 255) / 256) >= 64 ? 16 : 4;
+  const int64_t wide = ((int64_t)lay.k5s_tiles + 15) / 16 * ((net.Lp + 255) / 256);
+  return wide >= 512 || (wide >= 64 && net.K >= 1024) ? 16 : 4;
 }
 inline int screen_splits(const DevNet& net, const WsLayout& lay) {
   const int g = screen_tiles(net, lay);
   const int64_t blocks = (int64_t)((lay.k5s_tiles + g - 1) / g) * ((net.Lp + 255) / 256);
+  if (blocks >= 384) return 1;
   return (int)std::max<int64_t>(1, std::min<int64_t>(kScreenBlocks / blocks, (net.K + kScreenChunk - 1) / kScreenChunk));
 }
 
