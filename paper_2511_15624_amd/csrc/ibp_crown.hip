@@ -1039,6 +1039,223 @@ __global__ __launch_bounds__(256, MINB) void kc1c_chord(DevNet net, void* ws, Ws
   }
 }
 
+// The chord sweep of many boxes by outages: a wave's lanes hold 64 outages of two boxes
+// and walk the 1024 lines of the line tile.  Whether an element contributes (t_hi > 0)
+// takes five of its 57 instructions, and it depends on the line and the box far more than
+// on the outage (2000 buses, sub-boxes: a fifth of the elements), so whole waves skip the
+// rest; with the lanes over lines, as in kc1c_chord, every wave holds such a line.
+//
+// The elements, their four-line sums and the tree that adds 64 quads of lines in float32
+// are kc1c_chord's (halving_sum32 adds lanes i and i + 32 first): quads come in
+// bit-reversed order, and a stack of partial sums merges them like a binary counter.
+// Line data come as records (centre, h and g of a quad for each box) by scalar loads, in
+// the memory of the base-flow partials, which are dead by then.  The slopes of a line
+// and box, a lane each, wait in LDS until sixteen such rows are added up together (a
+// reduction of its own per line took half of the sweep's instructions).
+//
+// 1024 sub-boxes at 2000 buses 9.6 -> 3.9 ms, 64 at 8316 buses 6.9 -> 2.7 ms; one box
+// per wave 4.6 ms (factors read twice), four 6.2 (two waves per SIMD).  Below about 2048
+// waves the per-line sweep's smaller units fill the chip better: 64 boxes at 500 buses
+// (352 waves) 63 against 163 us, 16 at 2000 buses (1600 waves) the same.
+constexpr int kChordS = 2;  // boxes per wave
+constexpr int64_t kChordWaves = 2048;
+
+__global__ __launch_bounds__(256) void kc1s_records(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
+  const int64_t b = blockIdx.x;  // box, up to the next multiple of kChordS
+  const int64_t bb = min(b, n_box - 1);
+  const int q = blockIdx.y * 256 + threadIdx.x, Lp4 = net.Lp / 4;
+  if (q >= Lp4) return;
+  const double* bs = ws_ptr<double>(ws, lay.box) + bb * kBoxSlots;
+  const float vmax = __uint_as_float(*reinterpret_cast<const unsigned int*>(bs + kVmax));
+  const float4 e4 = reinterpret_cast<const float4*>(net.line_eps)[q];
+  const float ex = next_up_f32(e4.x * vmax), ey = next_up_f32(e4.y * vmax);
+  const float ez = next_up_f32(e4.z * vmax), ew = next_up_f32(e4.w * vmax);
+  const float4 c = reinterpret_cast<const float4*>(ws_ptr<float>(ws, lay.lc) + bb * net.Lp)[q];
+  const float4 h = reinterpret_cast<const float4*>(ws_ptr<float>(ws, lay.lh) + bb * net.Lp)[q];
+  const float4 g = reinterpret_cast<const float4*>(ws_ptr<float>(ws, lay.lg) + bb * net.Lp)[q];
+  float4* out = ws_ptr<float4>(ws, lay.part2) + (((b / kChordS) * Lp4 + q) * kChordS + b % kChordS) * 3;
+  out[0] = c;
+  out[1] = make_float4(add_ru(h.x, ex), add_ru(h.y, ey), add_ru(h.z, ez), add_ru(h.w, ew));
+  out[2] = make_float4(add_ru(g.x, ex), add_ru(g.y, ey), add_ru(g.z, ez), add_ru(g.w, ew));
+}
+
+constexpr int kChordRows = 16;      // (line, box) rows of slopes a wave collects before it adds them up
+constexpr int kChordStride = 64 + 16;  // words of a row: the sixteen lanes of a read step meet all banks
+
+__global__ __launch_bounds__(256, 5) void kc1s_chord(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
+  constexpr int S = kChordS;
+  __shared__ __align__(16) int rows_all[4][kChordRows * kChordStride];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t tile = (int64_t)blockIdx.x * 4 + w, b0 = tile * S;
+  if (b0 >= n_box) return;  // no block barrier follows
+  int* rows = rows_all[w];
+  const int k = blockIdx.z * 64 + lane;
+  const int Lp4 = net.Lp / 4;
+  float cc[S], rk[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) {
+    const int4 d = ws_ptr<int4>(ws, lay.ctg)[min(b0 + i, n_box - 1) * net.K + min(k, net.K - 1)];
+    // lanes past the last outage and boxes past the end: NaN fails every test
+    cc[i] = k < net.K && b0 + i < n_box ? __int_as_float(d.y) : NAN;
+    rk[i] = __int_as_float(d.z);
+  }
+  typedef __attribute__((address_space(4))) const float const_float;
+  const_float* rec = (const_float*)(ws_ptr<float>(ws, lay.part2) + (size_t)tile * Lp4 * S * 12);
+  const_float* lim = (const_float*)net.fmax_c32;
+  const float* __restrict__ lamT = net.lodfT + blockIdx.z * 64;
+  unsigned long long* cnt = ws_ptr<unsigned long long>(ws, lay.ccnt) + 2 * b0 * net.Lp;
+  // slope rows: the signed slopes of one line and box, a lane each; their sum and
+  // the sum of their magnitudes, four lanes a row
+  const int row_of = lane >> 2;
+  int n_row = 0, row_id = 0;
+  auto flush = [&] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int part = lane & 3;
+    const int4* p = reinterpret_cast<const int4*>(rows + row_of * kChordStride) + part;
+    int ts = 0, ta = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int4 v = p[4 * u];
+      ts += (v.x + v.y) + (v.z + v.w);
+      ta += (max(v.x, -v.x) + max(v.y, -v.y)) + (max(v.z, -v.z) + max(v.w, -v.w));
+    }
+    ts += __builtin_amdgcn_update_dpp(0, ts, kDppXor1, 0xF, 0xF, false);
+    ta += __builtin_amdgcn_update_dpp(0, ta, kDppXor1, 0xF, 0xF, false);
+    ts += __builtin_amdgcn_update_dpp(0, ts, kDppXor2, 0xF, 0xF, false);
+    ta += __builtin_amdgcn_update_dpp(0, ta, kDppXor2, 0xF, 0xF, false);
+    if (row_of < n_row && part < 2 && ta != 0)
+      atomicAdd(&cnt[2 * (size_t)row_id + part], (unsigned long long)(long long)(part ? ta : ts));
+    n_row = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+  double o[S][4];
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+#pragma unroll
+    for (int f = 0; f < 4; ++f) o[i][f] = 0.0;
+  constexpr float kDown = 1.0f - 0x1p-22f;
+  // a quad's factors, line records and limits, one quad ahead of their use
+  auto load = [&](int q, float (&x)[4], float (&v)[S][12], float (&t)[4]) {
+    const int l = 4 * min(q, Lp4 - 1);
+    const_float* rp = rec + (size_t)l * S * 3;
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+      for (int j = 0; j < 12; ++j) v[i][j] = rp[12 * i + j];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = lim[l + j];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] = (lamT + (size_t)min(l + j, net.L - 1) * net.Kp)[lane];
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto quad_of = [](int n) { return (int)(__brev((unsigned)n & 63u) >> 26); };
+  // one quad of lines: every box's four sums
+  auto leaf = [&](int q, const float (&x)[4], float (&v)[S][12], float (&t)[4], float (&cur)[S][4]) {
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+      for (int f = 0; f < 4; ++f) cur[i][f] = 0.0f;
+    if (q >= Lp4) return;
+    // loaded here, not where they are used
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+      for (int j = 0; j < 12; ++j) asm volatile("" : "+s"(v[i][j]));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) asm volatile("" : "+s"(t[j]));
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      uint64_t m[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float C = fmaf(x[j], cc[i], v[i][j]);
+        m[j] = __builtin_amdgcn_ballot_w64(fabsf(C) + fmaf(fabsf(x[j]), rk[i], v[i][4 + j]) > 0.0f);
+      }
+      if ((m[0] | m[1] | m[2] | m[3]) == 0) continue;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (m[j] == 0) continue;
+        float qa, qs, mm, tq = t[j] * kDown;
+        asm("" : "+v"(tq));  // rounded, as the per-line sweep holds it: not a factor of an fma
+        chord_elem(x[j], cc[i], rk[i], v[i][j], v[i][4 + j], v[i][8 + j], tq, qa, qs, mm);
+        const float a = qs * (1.0f / kSlopeQ);
+        const float p = a * finite_factor(x[j]);
+        cur[i][0] += p;
+        cur[i][1] += fabsf(p);
+        cur[i][2] += fabsf(a);
+        cur[i][3] += mm;
+        rows[n_row * kChordStride + lane] = (int)qs;
+        if (row_of == n_row) row_id = i * net.Lp + 4 * q + j;
+        if (++n_row == kChordRows) flush();
+      }
+    }
+  };
+  for (int g = 0; g < 4; ++g) {
+    const int q0 = (blockIdx.y * 4 + g) * 64;
+    if (q0 >= Lp4) break;
+    float st[5][S][4], even[S][4], odd[S][4];
+    float xe[4], xo[4], ve[S][12], vo[S][12], te[4], to[4];
+    load(q0 + quad_of(0), xe, ve, te);
+    for (int n = 0; n < 64; n += 2) {
+      load(q0 + quad_of(n + 1), xo, vo, to);
+      leaf(q0 + quad_of(n), xe, ve, te, even);
+      load(q0 + quad_of(n + 2), xe, ve, te);
+      leaf(q0 + quad_of(n + 1), xo, vo, to, odd);
+      // merge: the quads so far, as a binary counter of pairs
+      auto add = [&](const float (&t)[S][4]) {
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+          for (int f = 0; f < 4; ++f) even[i][f] = t[i][f] + even[i][f];
+      };
+      auto put = [&](float (&t)[S][4]) {
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+          for (int f = 0; f < 4; ++f) t[i][f] = even[i][f];
+      };
+      add(odd);
+      if (!(n & 2)) {
+        put(st[0]);
+        continue;
+      }
+      add(st[0]);
+      if (!(n & 4)) {
+        put(st[1]);
+        continue;
+      }
+      add(st[1]);
+      if (!(n & 8)) {
+        put(st[2]);
+        continue;
+      }
+      add(st[2]);
+      if (!(n & 16)) {
+        put(st[3]);
+        continue;
+      }
+      add(st[3]);
+      if (!(n & 32)) {
+        put(st[4]);
+        continue;
+      }
+      add(st[4]);
+    }
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+#pragma unroll
+      for (int f = 0; f < 4; ++f) o[i][f] += (double)even[i][f];
+  }
+  if (n_row > 0) flush();
+  if (k >= net.K) return;
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+    if (b0 + i < n_box)
+      ws_ptr<double4>(ws, lay.cv)[((size_t)(b0 + i) * lay.kc_bx + blockIdx.y) * net.K + k] =
+          make_double4(o[i][0], o[i][1], o[i][2], o[i][3]);
+}
+
 // Per line of the chord relaxation: the base line's chord (float64), the
 // adjoint v with vabs >= |v_exact| and ev >= |v^ - v_exact| as in KC2, and an
 // upper bound T_l on the line's share of the relaxation's constant:
@@ -1188,10 +1405,17 @@ hipError_t launch_crown_lower(const DevNet& net, int64_t n_box, const float* lo,
   if (net.K > 0) {
     const int t = tm->start(10, s);
     const unsigned kz = (unsigned)((net.K + kCKB - 1) / kCKB);
+    const int64_t waves = (n_box + kChordS - 1) / kChordS * lay.kc_bx * ((net.K + 63) / 64);
     if (n_box < kCB)
       hipLaunchKernelGGL((kc1c_chord<1, 5, kCKB1>), dim3((unsigned)n_box, lay.kc_bx, lay.chp_z), dim3(256), 0, s,
                          net, ws, lay, n_box);
-    else if (lay.chord_nb == 1)
+    else if (lay.chord_nb == 1 && waves >= kChordWaves) {
+      const int64_t tiles = (n_box + kChordS - 1) / kChordS;
+      hipLaunchKernelGGL(kc1s_records, dim3((unsigned)(kChordS * tiles), (net.Lp / 4 + 255) / 256), dim3(256), 0, s,
+                         net, ws, lay, n_box);
+      hipLaunchKernelGGL(kc1s_chord, dim3((unsigned)((tiles + 3) / 4), lay.kc_bx, (unsigned)((net.K + 63) / 64)),
+                         dim3(256), 0, s, net, ws, lay, n_box);
+    } else if (lay.chord_nb == 1)
       hipLaunchKernelGGL((kc1c_chord<1, 5, kCKB>), dim3((unsigned)n_box, lay.kc_bx, kz), dim3(256), 0, s, net, ws,
                          lay, n_box);
     else if (lay.chord_nb == 2)
