@@ -131,66 +131,83 @@ __device__ __forceinline__ void line_radii(const DevNet& net, void* ws, const Ws
   rp4 = make_float4(r0 + f4.x, r1 + f4.y, r2 + f4.z, r3 + f4.w);
 }
 
-__global__ __launch_bounds__(256) void k5_outage_vjp(DevNet net, void* ws, WsLayout lay, int64_t box0,
+// One box: a block takes 256 lines and kK5Chunk outages, each of its eight waves sixteen
+// of them, with all their factors in flight and one butterfly for their sums; the
+// waves' line sums meet in LDS.  (Four line tiles per block and 128 outages per wave, one
+// after the other, took 62 us at 2000 buses and 44 at 500, a wave's latency, against 18
+// and 10; 8316 buses 122 against 106, 4.2 TB/s and as much arithmetic.)  The
+// outage's values are read by every element's instructions: vector copies.
+__global__ __launch_bounds__(512) void k5_outage_vjp(DevNet net, void* ws, WsLayout lay, int64_t box0,
                                                      const double* __restrict__ g_lo,
                                                      const double* __restrict__ g_hi) {
+  static_assert(kK5Chunk == 8 * kK5Sub, "a sub-step per wave");
+  __shared__ float sh[8][8][64];
+  __shared__ float4 out[2][64];
   const int64_t b = box0 + blockIdx.z;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int tile = blockIdx.x * 4 + w;
+  const int tile = blockIdx.x;
   const int col = tile * 64 + lane;
   const int Lp4 = net.Lp / 4;
-  if (tile * 64 >= Lp4) return;  // whole wave beyond the lines (uniform)
   const bool on = col < Lp4;
-  const int k0 = blockIdx.y * kK5Chunk;
-  const int k1 = min(net.K, k0 + kK5Chunk);
-  const float chi = (float)(-net.zeta_f * (g_lo ? g_lo[b] : 0.0));  // weight of an active P_hi
-  const float clo = (float)(-net.zeta_f * (g_hi ? g_hi[b] : 0.0));  // weight of an active P_lo (dR gets -clo)
-  // lines of this lane (padding lines: zero centre and radius, limit FLT_MAX)
-  float4 c4 = make_float4(0.f, 0.f, 0.f, 0.f), rm4, rp4;
-  line_radii(net, ws, lay, b, col, on, c4, rm4, rp4);
-  const int4* cd = ws_ptr<int4>(ws, lay.ctg) + b * net.K;
-  const float4* lam = reinterpret_cast<const float4*>(net.lodf) + col;
-  float2* cpart = ws_ptr<float2>(ws, lay.cpart) + ((size_t)b * lay.k5_tiles + tile) * net.K;
-  double gcl[4] = {0, 0, 0, 0}, grl[4] = {0, 0, 0, 0};
-  for (int ks = k0; ks < k1; ks += kK5Sub) {
+  const int ks = blockIdx.y * kK5Chunk + w * kK5Sub;
+  const int k1 = min(net.K, ks + kK5Sub);
+  float gc[4] = {0, 0, 0, 0}, gr[4] = {0, 0, 0, 0};
+  if (ks < k1) {
+    // rows past the last outage read that one; lanes past the last column the last
+    // column, whose radii keep every test false
+    const float4* lam = reinterpret_cast<const float4*>(net.lodf) + (on ? col : Lp4 - 1);
+    float4 x[kK5Sub];
+#pragma unroll
+    for (int i = 0; i < kK5Sub; ++i) x[i] = ld_stream(lam + (size_t)min(ks + i, k1 - 1) * Lp4);
+    __builtin_amdgcn_sched_barrier(0);
+    const float chi = vcopy((float)(-net.zeta_f * (g_lo ? g_lo[b] : 0.0)));  // weight of an active P_hi
+    const float clo = vcopy((float)(-net.zeta_f * (g_hi ? g_hi[b] : 0.0)));  // weight of an active P_lo (dR gets -clo)
+    // lines of this lane (padding lines: zero centre and radius, limit FLT_MAX)
+    float4 c4 = make_float4(0.f, 0.f, 0.f, 0.f), rm4, rp4;
+    line_radii(net, ws, lay, b, col, on, c4, rm4, rp4);
+    const int4* cd = ws_ptr<int4>(ws, lay.ctg) + b * net.K;
     float v[32];
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = 0.0f;
-    float gc[4] = {0, 0, 0, 0}, gr[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < kK5Sub; ++i) {
-      const int k = ks + i;
-      if (k < k1) {  // uniform
-        const int4 d = cd[k];
-        const float cc = __int_as_float(d.y), rc = __int_as_float(d.w);
-        const float4 x = on ? lam[(size_t)k * Lp4] : make_float4(0.f, 0.f, 0.f, 0.f);
+      if (ks + i < k1) {  // uniform
+        const int4 d = cd[ks + i];
+        const float cc = vcopy(__int_as_float(d.y)), rc = vcopy(__int_as_float(d.w));
+        const float l0 = finite_factor(x[i].x), l1 = finite_factor(x[i].y), l2 = finite_factor(x[i].z),
+                    l3 = finite_factor(x[i].w);
         float pc = 0.0f, pr = 0.0f;
-        k5_elem<3>(x.x, finite_factor(x.x), cc, rc, c4.x, rm4.x, rp4.x, chi, clo, gc[0], gr[0], pc, pr);
-        k5_elem<3>(x.y, finite_factor(x.y), cc, rc, c4.y, rm4.y, rp4.y, chi, clo, gc[1], gr[1], pc, pr);
-        k5_elem<3>(x.z, finite_factor(x.z), cc, rc, c4.z, rm4.z, rp4.z, chi, clo, gc[2], gr[2], pc, pr);
-        k5_elem<3>(x.w, finite_factor(x.w), cc, rc, c4.w, rm4.w, rp4.w, chi, clo, gc[3], gr[3], pc, pr);
+        k5_elem<3>(x[i].x, l0, cc, rc, c4.x, rm4.x, rp4.x, chi, clo, gc[0], gr[0], pc, pr);
+        k5_elem<3>(x[i].y, l1, cc, rc, c4.y, rm4.y, rp4.y, chi, clo, gc[1], gr[1], pc, pr);
+        k5_elem<3>(x[i].z, l2, cc, rc, c4.z, rm4.z, rp4.z, chi, clo, gc[2], gr[2], pc, pr);
+        k5_elem<3>(x[i].w, l3, cc, rc, c4.w, rm4.w, rp4.w, chi, clo, gc[3], gr[3], pc, pr);
         v[2 * i] = pc;
         v[2 * i + 1] = pr;
       }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      gcl[j] += (double)gc[j];
-      grl[j] += (double)gr[j];
     }
     const float tot = butterfly32(v);
     const int idx = lane >> 1;  // value index: outage ks + idx / 2, field idx % 2
     const int k = ks + (idx >> 1);
     if ((lane & 1) == 0 && k < k1) {
-      float* dst = reinterpret_cast<float*>(cpart + k);
-      dst[idx & 1] = tot;
+      float2* cpart = ws_ptr<float2>(ws, lay.cpart) + ((size_t)b * lay.k5_tiles + tile) * net.K;
+      reinterpret_cast<float*>(cpart + k)[idx & 1] = tot;
     }
   }
-  if (on) {
-    float2* lp = ws_ptr<float2>(ws, lay.lpart) + ((size_t)b * lay.k5_by + blockIdx.y) * net.Lp + 4 * col;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) lp[j] = make_float2((float)gcl[j], (float)grl[j]);
+  for (int j = 0; j < 4; ++j) {
+    sh[w][2 * j][lane] = gc[j];
+    sh[w][2 * j + 1][lane] = gr[j];
+  }
+  __syncthreads();
+  double t = 0.0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) t += (double)sh[u][w][lane];
+  reinterpret_cast<float*>(&out[w >> 2][lane])[w & 3] = (float)t;  // value w: line w / 2, field w % 2
+  __syncthreads();
+  if (w < 2 && on) {
+    float2* lp = ws_ptr<float2>(ws, lay.lpart) + ((size_t)b * lay.k5_by + blockIdx.y) * net.Lp + 4 * col;
+    reinterpret_cast<float4*>(lp)[w] = out[w][lane];
   }
 }
 
@@ -766,44 +783,54 @@ __global__ __launch_bounds__(256) void k5r_lines(DevNet net, void* ws, WsLayout 
   grf[l] = (float)dr;
 }
 
-// Per bus (two buses per wave): d c_inj = Phi^T d c_f, d r_inj = |Phi|^T d r_f.
-__global__ __launch_bounds__(256) void k6_ptdf_t(DevNet net, void* ws, WsLayout lay, int64_t box0) {
+// Four buses per block: d c_inj = Phi^T d c_f, d r_inj = |Phi|^T d r_f.  The eight waves
+// share the buses' rows by columns, so the line gradients are read once for four
+// rows, four row loads are in flight per wave, and a block that comes last is short
+// (two whole rows per wave: 88 us at 8316 buses, 76 so, 6.1 TB/s; eight buses 79).
+constexpr int kK6Buses = 4;
+
+__global__ __launch_bounds__(512) void k6_ptdf_t(DevNet net, void* ws, WsLayout lay, int64_t box0) {
+  __shared__ double sh[8][2 * kK6Buses];
   const int64_t b = box0 + blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
-  const int n0 = (blockIdx.x * 4 + w) * 2;
-  if (n0 >= net.Np) return;
+  const int n0 = blockIdx.x * kK6Buses;
   const int Lp4 = net.Lp / 4;
   const float4* gc = reinterpret_cast<const float4*>(ws_ptr<float>(ws, lay.gcf) + b * net.Lp);
   const float4* gr = reinterpret_cast<const float4*>(ws_ptr<float>(ws, lay.grf) + b * net.Lp);
-  const bool two = n0 + 1 < net.N;
-  const float4* p0 = reinterpret_cast<const float4*>(net.phiT) + (size_t)min(n0, net.N - 1) * Lp4;
-  const float4* p1 = reinterpret_cast<const float4*>(net.phiT) + (size_t)min(n0 + 1, net.N - 1) * Lp4;
-  float a0 = 0, q0 = 0, a1 = 0, q1 = 0;
-  if (n0 < net.N) {
-    for (int j = lane; j < Lp4; j += 64) {
-      const float4 c = gc[j], r = gr[j];
-      const float4 x = ld_stream(p0 + j);
-      a0 = fmaf(x.x, c.x, fmaf(x.y, c.y, fmaf(x.z, c.z, fmaf(x.w, c.w, a0))));
-      q0 = fmaf(fabsf(x.x), r.x, fmaf(fabsf(x.y), r.y, fmaf(fabsf(x.z), r.z, fmaf(fabsf(x.w), r.w, q0))));
-      if (two) {
-        const float4 y = ld_stream(p1 + j);
-        a1 = fmaf(y.x, c.x, fmaf(y.y, c.y, fmaf(y.z, c.z, fmaf(y.w, c.w, a1))));
-        q1 = fmaf(fabsf(y.x), r.x, fmaf(fabsf(y.y), r.y, fmaf(fabsf(y.z), r.z, fmaf(fabsf(y.w), r.w, q1))));
-      }
+  const float4* p[kK6Buses];
+  float a[kK6Buses], q[kK6Buses];
+#pragma unroll
+  for (int i = 0; i < kK6Buses; ++i) {
+    p[i] = reinterpret_cast<const float4*>(net.phiT) + (size_t)min(n0 + i, net.N - 1) * Lp4;
+    a[i] = q[i] = 0.0f;
+  }
+  for (int j = threadIdx.x; j < Lp4; j += 512) {
+    float4 x[kK6Buses];
+#pragma unroll
+    for (int i = 0; i < kK6Buses; ++i) x[i] = ld_stream(p[i] + j);
+    const float4 c = gc[j], r = gr[j];
+#pragma unroll
+    for (int i = 0; i < kK6Buses; ++i) {
+      a[i] = fmaf(x[i].x, c.x, fmaf(x[i].y, c.y, fmaf(x[i].z, c.z, fmaf(x[i].w, c.w, a[i]))));
+      q[i] = fmaf(fabsf(x[i].x), r.x, fmaf(fabsf(x[i].y), r.y, fmaf(fabsf(x[i].z), r.z, fmaf(fabsf(x[i].w), r.w, q[i]))));
     }
   }
-  const double s0 = wave_sum((double)a0), t0 = wave_sum((double)q0);
-  const double s1 = wave_sum((double)a1), t1 = wave_sum((double)q1);
-  if (lane == 0) {
-    double* gci = ws_ptr<double>(ws, lay.gci) + b * net.Np;
-    double* gri = ws_ptr<double>(ws, lay.gri) + b * net.Np;
-    gci[n0] = n0 < net.N ? s0 : 0.0;
-    gri[n0] = n0 < net.N ? t0 : 0.0;
-    if (n0 + 1 < net.Np) {
-      gci[n0 + 1] = two ? s1 : 0.0;
-      gri[n0 + 1] = two ? t1 : 0.0;
+#pragma unroll
+  for (int i = 0; i < kK6Buses; ++i) {
+    const double s = wave_sum((double)a[i]), t = wave_sum((double)q[i]);
+    if (lane == 0) {
+      sh[w][2 * i] = s;
+      sh[w][2 * i + 1] = t;
     }
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 * kK6Buses) {
+    double t = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t += sh[u][threadIdx.x];
+    const int n = n0 + (threadIdx.x >> 1);
+    if (n < net.Np) ws_ptr<double>(ws, (threadIdx.x & 1) ? lay.gri : lay.gci)[b * net.Np + n] = n < net.N ? t : 0.0;
   }
 }
 
@@ -1121,7 +1148,7 @@ hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, co
     const int nb = (int)std::min<int64_t>(65535, n_box - b0);
     if (net.K > 0 && !(n_box >= kBatchMin && lay.batched)) {
       const int t = tm->start(7, s);
-      hipLaunchKernelGGL(k5_outage_vjp, dim3((lay.k5_tiles + 3) / 4, lay.k5_by, nb), dim3(256), 0, s, net, ws,
+      hipLaunchKernelGGL(k5_outage_vjp, dim3(lay.k5_tiles, lay.k5_by, nb), dim3(512), 0, s, net, ws,
                          lay, b0, g_lo, g_hi);
       tm->stop(t, s);
     }
@@ -1151,7 +1178,7 @@ hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, co
     int t;
     if (n_box < kBatchMin) {
       t = tm->start(8, s);
-      hipLaunchKernelGGL(k6_ptdf_t, dim3((net.Np + 7) / 8, nb), dim3(256), 0, s, net, ws, lay, b0);
+      hipLaunchKernelGGL(k6_ptdf_t, dim3((net.Np + kK6Buses - 1) / kK6Buses, nb), dim3(512), 0, s, net, ws, lay, b0);
       tm->stop(t, s);
     }
     t = tm->start(9, s);
