@@ -198,14 +198,16 @@ __global__ __launch_bounds__(256) void kn_outages(DevNet net, void* ws, WsLayout
 //    bounds agree to 1e-9 (65 networks of 1000 to 8300 buses, sub-boxes, periods and
 //    whole boxes).  18432 boxes at 2000 buses: 3.1 ms (kHeavy = 3: 4.7, 2: 9.9).
 // Blocks of one group of boxes run on one XCD, whose L2 then holds the group's
-// (c_k, r_k) (1.5 MB at 2954 outages).
+// (c_k, r_k) (1.5 MB at 2954 outages).  Loads and the float64 evaluations of the
+// candidates bound it together: four waves per SIMD (128 registers) take 4.0 ms for
+// 18432 boxes at 2000 buses, three (134 registers) 5.0, five (spills) 5.2.
 constexpr float kHeavy = 4.0f;
 constexpr float kTinyRadius = 0x1p-6f;
 constexpr int kList = 60;  // candidates of a line listed before they are evaluated
 constexpr int kNearRank = 4;  // of 64 sampled outages: the pair threshold is the 4th largest |Lam| w
 
 template <int SIDES>
-__global__ __launch_bounds__(256) void kn_lines(DevNet net, void* ws, WsLayout lay, int64_t n_box, int n_lb,
+__global__ __launch_bounds__(256, 4) void kn_lines(DevNet net, void* ws, WsLayout lay, int64_t n_box, int n_lb,
                                                 int n_units) {
   constexpr bool UP = SIDES & 2, LO = SIDES & 1;
   __shared__ __align__(16) union {
@@ -427,29 +429,31 @@ __global__ __launch_bounds__(256) void kn_lines(DevNet net, void* ws, WsLayout l
 #pragma unroll
   for (int j = 0; j < 8; ++j) lp[j] = net.lodfT + (size_t)min(l0 + w * 8 + j, net.L - 1) * net.Kp;
   int cnt[8] = {};
-  for (int kc = 0;; kc += 2) {
+  // the next 64 outages' factors are loaded while these are tested
+  float ln[8], wn = W[lane];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ln[j] = lp[j][lane];
+  for (int kc = 0;; ++kc) {
     const bool last = kc >= n_kc;
     if (!last) {
-      const int ka = kc * 64 + lane, kb = min(kc + 1, n_kc - 1) * 64 + lane;
-      const float wa = W[ka], wb = kc + 1 < n_kc ? W[kb] : 0.0f;
-      float la[8], lb8[8];
+      const int k = kc * 64 + lane, kn = min(kc + 1, n_kc - 1) * 64 + lane;
+      const float wk = wn;
+      float la[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) la[j] = ln[j];
+      wn = W[kn];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) ln[j] = lp[j][kn];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        la[j] = lp[j][ka];
-        lb8[j] = lp[j][kb];
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          // (a line's own outage is NaN: false)
-          const uint64_t mask = __builtin_amdgcn_ballot_w64(fabsf(lin_factor(r ? lb8[j] : la[j])) * (r ? wb : wa) > mg[j]);
-          if (mask == 0) continue;
-          const int rank =
-              __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-          if ((mask >> lane) & 1) lst[j][cnt[j] + rank] = r ? kb : ka;
-          cnt[j] = __builtin_amdgcn_readfirstlane(cnt[j] + __builtin_popcountll(mask));
-        }
+        // (a line's own outage is NaN: false)
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(fabsf(lin_factor(la[j])) * wk > mg[j]);
+        if (mask == 0) continue;
+        const int rank =
+            __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+        if ((mask >> lane) & 1) lst[j][cnt[j] + rank] = k;
+        cnt[j] = __builtin_amdgcn_readfirstlane(cnt[j] + __builtin_popcountll(mask));
       }
     }
 #pragma unroll
