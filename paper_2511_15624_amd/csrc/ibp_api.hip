@@ -494,6 +494,13 @@ void add_screen(const ibp::DevNet& d, const ibp::Tune& tune, int64_t n_box, ibp:
   };
   lay.k5s_tiles = (int)((B + ibp::kScreenBoxes - 1) / ibp::kScreenBoxes);
   const size_t tiles = (size_t)lay.k5s_tiles;
+  // at most 64 groups, whose masks then fit in the memory of the base-flow partials
+  // (dead when the screen runs): 8 Lp bytes per four boxes of 64 Lp
+  lay.cm_shift = 0;
+  auto groups = [&] { return (int)(((int64_t)d.K + (256ll << lay.cm_shift) - 1) / (256ll << lay.cm_shift)); };
+  while (groups() > 64) ++lay.cm_shift;
+  lay.cm_groups = groups();
+  lay.cmask = at ? take(tiles * lay.cm_groups * (d.Lp / 64) * sizeof(uint64_t)) : lay.part2;
   lay.smask = take(tiles * (d.Lp / 64) * sizeof(uint64_t));
   lay.srec = take(tiles * d.Lp * ibp::kScreenRecFloats * sizeof(float));
   lay.k5w_bx = (d.Kp + 255) / 256;

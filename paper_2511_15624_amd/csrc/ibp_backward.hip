@@ -538,7 +538,9 @@ __global__ __launch_bounds__(256) void k5p_sweep(DevNet net, void* ws, WsLayout 
   const int per_seg = (net.Lp / 64 + n_seg - 1) / n_seg, word0 = seg * per_seg;
   const int words = min(per_seg, net.Lp / 64 - word0);  // of this segment (may be none)
   if (on) {
-    const uint64_t* mask = ws_ptr<uint64_t>(ws, lay.smask) + (size_t)tile * (net.Lp / 64) + word0;
+    const int group = (kw >> 8) >> lay.cm_shift;  // of this wave's outages
+    const uint64_t* mask =
+        ws_ptr<uint64_t>(ws, lay.cmask) + ((size_t)tile * lay.cm_groups + group) * (net.Lp / 64) + word0;
     for (int j = lane; j < words; j += 64) smk[j] = mask[j];
   }
   __syncthreads();

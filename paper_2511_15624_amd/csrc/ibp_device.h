@@ -116,6 +116,8 @@ struct WsLayout : FwdLayout {
   int k5s_tiles = 0;               // tiles of kScreenBoxes boxes (0: not laid out)
   int fscreen = 0;                 // one-sided box-tiled forward calls take the screened sweep
   size_t smask = 0;                // uint64 [tiles][Lp / 64]: candidate-line bit masks
+  size_t cmask = 0;                // uint64 [tiles][cm_groups][Lp / 64]: the same masks per group of outages
+  int cm_groups = 0, cm_shift = 0; // groups of 256 << cm_shift outages
   size_t srec = 0;                 // float [tiles][Lp][12]: the tile's boxes' centres and radius terms
   size_t lcnt = 0;                 // uint64 [B][Lp]: active-element counts (negative-flow count << 32 | count)
   size_t sw = 0;                   // float [tiles][Kp]: per tile and outage, max over its boxes of max(|c_c| - r_c, 0)

@@ -41,18 +41,18 @@
 
 namespace ibp {
 
-constexpr int kScreenChunk = 128;  // outages per LDS chunk of the screen
+constexpr int kScreenChunk = 64;  // outages per LDS chunk of the screen
 
 // Tiles per screen block: sixteen share every factor load where outages are many (1024
-// boxes at 2000 buses, with the split below 0.21 ms; four and no split 0.42) or
-// blocks too; with few outages the marks are the work, and four finish earlier (2533 boxes
-// at 529 buses 79 against 96 us, 14160 at 20 buses 12 against 33).
+// boxes at 2000 buses, with the split below 0.17 ms; four and no split 0.42) or
+// blocks too; with few outages the marks are the work, and four finish earlier (14160
+// boxes at 20 buses 13 against 33 us).
 //
 // Outage ranges a line block and tile group is split over when those alone leave the
-// chip idle (below 384 blocks): partial maxima then meet in the first word of the tile's
-// line record, and k5s_mark takes the marks from there.  About kScreenBlocks blocks
-// (2000 buses, 8 boxes: 600 -> 30 us).
-constexpr int kScreenBlocks = 1024;
+// chip half idle (seven blocks fit a CU); k5s_mark then joins the ranges' masks.  4096 boxes at
+// 2000 buses 0.79 -> 0.50 ms and 0.07 for the join, 2533 at 529 buses 78 -> 33 us and 10, 8
+// at 2000 buses 600 -> 30 us.
+constexpr int kScreenBlocks = 1792;
 inline int screen_tiles(const DevNet& net, const WsLayout& lay) {
   const int64_t wide = ((int64_t)lay.k5s_tiles + 15) / 16 * ((net.Lp + 255) / 256);
   return wide >= 512 || (wide >= 64 && net.K >= 1024) ? 16 : 4;
@@ -60,8 +60,8 @@ inline int screen_tiles(const DevNet& net, const WsLayout& lay) {
 inline int screen_splits(const DevNet& net, const WsLayout& lay) {
   const int g = screen_tiles(net, lay);
   const int64_t blocks = (int64_t)((lay.k5s_tiles + g - 1) / g) * ((net.Lp + 255) / 256);
-  if (blocks >= 384) return 1;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(kScreenBlocks / blocks, (net.K + kScreenChunk - 1) / kScreenChunk));
+  if (2 * blocks > kScreenBlocks) return 1;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kScreenBlocks / blocks, lay.cm_groups));
 }
 
 // The per-outage (centre, radius) the sweep of `mode` uses: the backward's
@@ -99,7 +99,7 @@ __device__ __forceinline__ float line_g(const DevNet& net, void* ws, const WsLay
 // K5w: per tile and outage W (zero past the last outage); per tile and block
 // of 256 outages the largest |c_c| + r_c, for the margin.
 template <int MODE>
-__global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayout lay, int64_t n_box, int clear) {
+__global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
   constexpr int S = kScreenBoxes;
   __shared__ unsigned zs[4];
   const int k = blockIdx.x * 256 + threadIdx.x;
@@ -117,9 +117,6 @@ __global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayo
     }
   }
   if (k < net.Kp) ws_ptr<float>(ws, lay.sw)[t * net.Kp + k] = wv;
-  if (clear)  // the partial maxima's slots
-    for (int l = k; l < net.Lp; l += gridDim.x * 256)
-      ws_ptr<float>(ws, lay.srec)[((size_t)t * net.Lp + l) * kScreenRecFloats] = 0.0f;
   // non-negative floats order like their bit patterns
   const unsigned zb = wave_max_u32(__float_as_uint(z));
   if ((threadIdx.x & 63) == 0) zs[threadIdx.x >> 6] = zb;
@@ -129,38 +126,54 @@ __global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayo
         __uint_as_float(max(max(zs[0], zs[1]), max(zs[2], zs[3])));
 }
 
-// One line's mark in one tile from the largest |Lam| W of its outages: every lane
-// of the block's waves calls it with its own line (`lon`: a real line), wave-uniform
-// tile and margin scale z.
+// What |Lam| W has to exceed for an element of the line in one of the tile's boxes to
+// be active (lowered by the margin of the float32 roundings): z is the tile's largest
+// |c_c| + r_c.
+template <int MODE>
+__device__ __forceinline__ float line_threshold(const DevNet& net, void* ws, const WsLayout& lay, int64_t n_box,
+                                                int64_t t, int l, bool lon, float z, float fc, float amax) {
+  constexpr int S = kScreenBoxes;
+  const float* lc = ws_ptr<float>(ws, lay.lc);
+  float base = -FLT_MAX, sc = 0.0f;
+#pragma unroll
+  for (int i = 0; i < S; ++i) {
+    const int64_t b = t * S + i;
+    if (lon && b < n_box) {
+      const float c = lc[b * net.Lp + l], r = line_term<MODE>(net, ws, lay, b, l, fc);
+      base = fmaxf(base, MODE >= kScreenForwardUpper ? fabsf(c) + r : fabsf(c) - r);
+      sc = fmaxf(sc, fabsf(c) + fabsf(r));
+    }
+  }
+  const float margin = 0x1p-19f * (sc + amax * z);
+  return lon ? -margin - base : INFINITY;
+}
+
+// One line's mark in one tile and, if it is marked, its record: every lane of the
+// block's waves calls it with its own line.
 template <int MODE>
 __device__ __forceinline__ void mark_line(const DevNet& net, void* ws, const WsLayout& lay, int64_t n_box, int64_t t,
-                                          int l, bool lon, float m, float z, float fc, float amax) {
+                                          int l, bool flag, float fc) {
   constexpr int S = kScreenBoxes;
   static_assert(S == 4, "a tile's line record holds four boxes");
   // a box past the end gets a record that never tests active
   constexpr float kOff = MODE >= kScreenForwardUpper ? -INFINITY : INFINITY;
   const float* lc = ws_ptr<float>(ws, lay.lc);
   const int words = net.Lp / 64, word = l >> 6;
+  const uint64_t bits = __builtin_amdgcn_ballot_w64(flag);
+  if ((threadIdx.x & 63) == 0 && word < words) ws_ptr<uint64_t>(ws, lay.smask)[t * words + word] = bits;
+  if (!flag) return;
   float cv[S], rv[S], gv[S];
-  float base = -FLT_MAX, sc = 0.0f;
 #pragma unroll
   for (int i = 0; i < S; ++i) {
     const int64_t b = t * S + i;
     cv[i] = 0.0f;
     rv[i] = kOff;
     gv[i] = INFINITY;
-    if (lon && b < n_box) {
+    if (b < n_box) {
       cv[i] = lc[b * net.Lp + l];
       rv[i] = line_term<MODE>(net, ws, lay, b, l, fc);
-      base = fmaxf(base, MODE >= kScreenForwardUpper ? fabsf(cv[i]) + rv[i] : fabsf(cv[i]) - rv[i]);
-      sc = fmaxf(sc, fabsf(cv[i]) + fabsf(rv[i]));
     }
   }
-  const float margin = 0x1p-19f * (sc + amax * z);
-  const bool flag = lon && base + m > -margin;
-  const uint64_t bits = __builtin_amdgcn_ballot_w64(flag);
-  if ((threadIdx.x & 63) == 0 && word < words) ws_ptr<uint64_t>(ws, lay.smask)[t * words + word] = bits;
-  if (!flag) return;
   float4* rec = reinterpret_cast<float4*>(ws_ptr<float>(ws, lay.srec) + ((size_t)t * net.Lp + l) * kScreenRecFloats);
   rec[0] = make_float4(cv[0], cv[1], cv[2], cv[3]);
   rec[1] = make_float4(rv[0], rv[1], rv[2], rv[3]);
@@ -178,30 +191,44 @@ __device__ __forceinline__ void mark_line(const DevNet& net, void* ws, const WsL
 }
 
 // K5s: one line per lane, G tiles per block, the tiles' W staged in LDS
-// kScreenChunk outages at a time; outage range blockIdx.z of gridDim.z.
+// kScreenChunk outages at a time; outage range blockIdx.z of gridDim.z.  A line is
+// marked per group of 256 << cm_shift outages, the sweeps' chunks: a line that only
+// some outages move over its limit is walked for their chunks alone (8192 centre points
+// at 2000 buses: 35% of the lines are marked, 21% of the lines and chunks; their sweep
+// 3.4 -> 2.2 ms, that of the boxes 1.6 -> 1.05).  Waits for the factors and for W bound
+// the kernel: with seven waves per SIMD (72 registers, thresholds in LDS) 8192 boxes take
+// 1.04 ms, with four 1.35.
 template <int MODE, int G>
-__global__ __launch_bounds__(256) void k5s_screen(DevNet net, void* ws, WsLayout lay, int64_t n_box, int k_per) {
+__global__ __launch_bounds__(256, 7) void k5s_screen(DevNet net, void* ws, WsLayout lay, int64_t n_box, int k_per) {
   static_assert(G % 4 == 0, "tiles are read from LDS as float4");
   __shared__ __align__(16) float wsh[kScreenChunk][G];
-  __shared__ float zsh[G];
-  const int tid = threadIdx.x;
+  __shared__ float tsh[G][256];   // the thresholds (a group's end reads them)
+  float* zsh = &wsh[0][0];        // the tiles' margin scales, before the first chunk
+  const int tid = threadIdx.x, lane = tid & 63;
   const int l = blockIdx.x * 256 + tid;
   const bool lon = l < net.L;
-  const int lq = min(l, net.Lp - 1);
+  const int words = net.Lp / 64, word = l >> 6;
   const int64_t tile0 = (int64_t)blockIdx.y * G;
   const int ntile = (int)min<int64_t>(G, lay.k5s_tiles - tile0);
   const int kbeg = blockIdx.z * k_per, kend = min(net.K, kbeg + k_per);
   const float* W = ws_ptr<float>(ws, lay.sw) + tile0 * net.Kp;
-  if (tid < G && gridDim.z == 1) {
+  if (tid < G) {
     float z = 0.0f;
     if (tid < ntile)
       for (int j = 0; j < lay.k5w_bx; ++j) z = fmaxf(z, ws_ptr<float>(ws, lay.sz)[(tile0 + tid) * lay.k5w_bx + j]);
     zsh[tid] = z;
   }
+  __syncthreads();
+  const float fc = lon ? net.fmax_c32[l] : 0.0f, amax = lon ? net.lam_max[l] : 0.0f;
   float m[G];
 #pragma unroll
-  for (int g = 0; g < G; ++g) m[g] = 0.0f;
-  const float* lam = net.lodf + lq;
+  for (int g = 0; g < G; ++g) {
+    m[g] = 0.0f;
+    tsh[g][tid] = g < ntile ? line_threshold<MODE>(net, ws, lay, n_box, tile0 + g, l, lon, zsh[g], fc, amax) : INFINITY;
+  }
+  unsigned any = 0u;  // bit g: marked in some group
+  const int group = 256 << lay.cm_shift;
+  const float* lam = net.lodf + min(l, net.Lp - 1);
   for (int k0 = kbeg; k0 < kend; k0 += kScreenChunk) {
     const int nk = min(kScreenChunk, kend - k0);
     __syncthreads();
@@ -212,12 +239,12 @@ __global__ __launch_bounds__(256) void k5s_screen(DevNet net, void* ws, WsLayout
     __syncthreads();
     // |Lam| W: the outaged line's own factor is NaN, and fmaxf keeps m there;
     // rows past the chunk's end read its last row against W = 0
-    for (int kk = 0; kk < nk; kk += 4) {
-      float a[4];
+    for (int kk = 0; kk < nk; kk += 8) {
+      float a[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] = fabsf(lam[(size_t)(k0 + min(kk + u, nk - 1)) * net.Lp]);
+      for (int u = 0; u < 8; ++u) a[u] = fabsf(lam[(size_t)(k0 + min(kk + u, nk - 1)) * net.Lp]);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < 8; ++u) {
 #pragma unroll
         for (int g4 = 0; g4 < G / 4; ++g4) {
           const float4 wv = *reinterpret_cast<const float4*>(&wsh[kk + u][4 * g4]);
@@ -228,24 +255,20 @@ __global__ __launch_bounds__(256) void k5s_screen(DevNet net, void* ws, WsLayout
         }
       }
     }
-  }
-  if (gridDim.z > 1) {  // non-negative floats order like their bit patterns
-    if (lon)
+    const int k1 = k0 + kScreenChunk;
+    if (k1 < kend && k1 % group != 0) continue;
+    uint64_t* cm = ws_ptr<uint64_t>(ws, lay.cmask) + ((size_t)tile0 * lay.cm_groups + k0 / group) * words + word;
 #pragma unroll
-      for (int g = 0; g < G; ++g)
-        if (g < ntile)
-          atomicMax(reinterpret_cast<unsigned*>(ws_ptr<float>(ws, lay.srec) +
-                                                ((size_t)(tile0 + g) * net.Lp + l) * kScreenRecFloats),
-                    __float_as_uint(m[g]));
-    return;
+    for (int g = 0; g < G; ++g) {
+      const bool on = m[g] > tsh[g][tid];
+      const uint64_t bits = __builtin_amdgcn_ballot_w64(on);
+      if (lane == 0 && g < ntile && word < words) cm[(size_t)g * lay.cm_groups * words] = bits;
+      any |= on ? 1u << g : 0u;
+      m[g] = 0.0f;
+    }
   }
-  const float fc = lon ? net.fmax_c32[l] : 0.0f;
-  const float amax = lon ? net.lam_max[l] : 0.0f;
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    if (g >= ntile) break;  // uniform
-    mark_line<MODE>(net, ws, lay, n_box, tile0 + g, l, lon, m[g], zsh[g], fc, amax);
-  }
+  if (gridDim.z > 1) return;
+  for (int g = 0; g < ntile; ++g) mark_line<MODE>(net, ws, lay, n_box, tile0 + g, l, (any >> g) & 1u, fc);
 }
 
 // The marks of a screen that was split over the outages: one tile per block row.
@@ -253,20 +276,21 @@ template <int MODE>
 __global__ __launch_bounds__(256) void k5s_mark(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
   const int l = blockIdx.x * 256 + threadIdx.x;
   const int64_t t = blockIdx.y;
-  const bool lon = l < net.L;
-  float z = 0.0f;
-  for (int j = 0; j < lay.k5w_bx; ++j) z = fmaxf(z, ws_ptr<float>(ws, lay.sz)[t * lay.k5w_bx + j]);
-  const float m = lon ? ws_ptr<float>(ws, lay.srec)[((size_t)t * net.Lp + l) * kScreenRecFloats] : 0.0f;
-  mark_line<MODE>(net, ws, lay, n_box, t, l, lon, m, z, lon ? net.fmax_c32[l] : 0.0f, lon ? net.lam_max[l] : 0.0f);
+  const int words = net.Lp / 64, word = min(l >> 6, words - 1);
+  const uint64_t* cm = ws_ptr<uint64_t>(ws, lay.cmask) + (size_t)t * lay.cm_groups * words + word;
+  uint64_t any = 0;
+#pragma unroll 8
+  for (int j = 0; j < lay.cm_groups; ++j) any |= cm[(size_t)j * words];
+  mark_line<MODE>(net, ws, lay, n_box, t, l, l < net.L && ((any >> (l & 63)) & 1), l < net.L ? net.fmax_c32[l] : 0.0f);
 }
 
 template <int MODE>
 static void launch_screen_mode(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, hipStream_t s) {
   const int z = screen_splits(net, lay), g = screen_tiles(net, lay);
-  const int k_per = ((net.K + z - 1) / z + kScreenChunk - 1) / kScreenChunk * kScreenChunk;
+  const int group = 256 << lay.cm_shift;
+  const int k_per = ((net.K + z - 1) / z + group - 1) / group * group;
   const unsigned gx = (net.Lp + 255) / 256, gz = (unsigned)((net.K + k_per - 1) / k_per);
-  hipLaunchKernelGGL(k5w_tile_max<MODE>, dim3(lay.k5w_bx, lay.k5s_tiles), dim3(256), 0, s, net, ws, lay, n_box,
-                     (int)(gz > 1));
+  hipLaunchKernelGGL(k5w_tile_max<MODE>, dim3(lay.k5w_bx, lay.k5s_tiles), dim3(256), 0, s, net, ws, lay, n_box);
   const dim3 grid(gx, (lay.k5s_tiles + g - 1) / g, gz);
   if (g == 16)
     hipLaunchKernelGGL((k5s_screen<MODE, 16>), grid, dim3(256), 0, s, net, ws, lay, n_box, k_per);
@@ -317,7 +341,9 @@ __global__ __launch_bounds__(256) void k3p_sweep(DevNet net, void* ws, WsLayout 
   const int per_seg = (net.Lp / 64 + n_seg - 1) / n_seg, word0 = seg * per_seg;
   const int words = min(per_seg, net.Lp / 64 - word0);  // of this segment (may be none)
   if (on) {
-    const uint64_t* mask = ws_ptr<uint64_t>(ws, lay.smask) + (size_t)tile * (net.Lp / 64) + word0;
+    const int group = (kw >> 8) >> lay.cm_shift;  // of this wave's outages
+    const uint64_t* mask =
+        ws_ptr<uint64_t>(ws, lay.cmask) + ((size_t)tile * lay.cm_groups + group) * (net.Lp / 64) + word0;
     for (int j = lane; j < words; j += 64) smk[j] = mask[j];
   }
   __syncthreads();
