@@ -432,6 +432,7 @@ ibp_status to_device(ibp_network* net, int device) {
     if (const char* p = std::strstr(e, "k5s=")) t.k5_sparse = std::atoi(p + 4) != 0;
     if (const char* p = std::strstr(e, "k3s=")) t.k3_sparse = std::atoi(p + 4) != 0;
     if (const char* p = std::strstr(e, "k3l=")) t.k3_lin = std::atoi(p + 4) != 0;
+    if (const char* p = std::strstr(e, "mb=")) t.micro = std::atoi(p + 3) != 0;
     if (const char* p = std::strstr(e, "scru=")) t.k3_scr = std::atoi(p + 5) != 0;
     if (ibp::tune_valid(t) && ibp::tune_batched_valid(t) && (t.chord_nb == 1 || t.chord_nb == 2 || t.chord_nb == 4)) net->tune = t;
   }
@@ -562,7 +563,21 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
     return big;
   }
   const bool batched = n_box >= ibp::kBatchMin && !(flags & IBP_F_PLAIN);
-  ibp::WsLayout lay = layout_for(net, n_box, net->tune, batched);
+  // Small networks' two-sided bounds (also under the relaxations), one block per box: the
+  // base flows add the buses in the order the float64 matrix products do, and the
+  // outages pair as the box-tiled sweep's rows do, so that a line's or pair's float32
+  // rounding is the same there.
+  const ibp::Tune& tune = net->tune;
+  const bool micro = (flags & ~uint32_t(IBP_F_CROWN | IBP_F_CROWN_REF)) == 0 && batched && tune.micro &&
+                     tune.k2b_mfma && tune.k2_by == 0 && !tune.k3_scr && tune.k3_lin != 1 &&
+                     ibp::micro_pays(net->dn, n_box);
+  ibp::WsLayout lay = layout_for(net, n_box, net->tune, batched && !micro);
+  if (micro) {
+    ibp::WsLayout tiled;
+    ibp::plan_batched(net->dn, n_box, tiled, tune);
+    lay.k3_kper = tiled.k3_kper;
+    lay.k3_unit = 4;
+  }
   if (flags & (IBP_F_BACKWARD | IBP_F_KEEP_PREP)) {
     const ibp::DevNet& d = net->dn;
     const size_t B = (size_t)std::max<int64_t>(1, n_box);

@@ -699,15 +699,19 @@ __global__ __launch_bounds__(256) void k3_contingency(DevNet net, void* ws, FwdL
 // elements on: one block's time is its loads' latencies in a row (sixteen buses of a
 // column at a time, one item of the sweep at a time), so a wide block stages the
 // PTDF in LDS, a line per thread, and has the sweep's first items loaded from the
-// start.  One box, whole call: 57 buses 16.2 -> 13.7 us (the host's share), 107
-// buses 26.2 -> 16.4, 160 buses 39.8 -> 23.3; at 39 buses both are the host's 13.5.
-// The sums over buses keep their order.
+// start, a column of lines per thread.  One box, whole call: 57 buses 16.2 -> 13.9 us
+// (the host's share), 107 buses 26.2 -> 15.7, 160 buses 39.8 -> 20.5; at 39 buses both
+// are the host's 13.5.  The sums over buses keep their order.
 constexpr int kMicroBuses = 256;
 constexpr int kMicroLines = 1024;
 constexpr int kMicroElems = 65536;
 
 constexpr int kMicroStage = 16384;  // floats of PTDF rows that a wide block stages in LDS
 constexpr int64_t kMicroWideElems = 8192;
+
+static bool micro_net(const DevNet& net) {
+  return net.N <= kMicroBuses && net.L <= kMicroLines && (int64_t)net.K * net.Lp <= kMicroElems;
+}
 
 static bool micro_wide(const DevNet& net) { return (int64_t)(net.K + net.N) * net.Lp > kMicroWideElems; }
 
@@ -743,23 +747,33 @@ __global__ __launch_bounds__(T) void km_box(DevNet net, const float* __restrict_
     p3 = p[min(tid + 3 * T, nq - 1)];
   };
   if constexpr (WIDE) load_rows(0);
-  // outage sweep: items (column of four lines, pair of outages), columns fastest
-  const int np = SWEEP ? net.K / 2 : 0;
-  const float4* lam = reinterpret_cast<const float4*>(net.lodf);
+  // outage sweep: a thread has one column of four lines and every per-th slot of two
+  // outages; slot t is the (t % spr)-th of row t / spr (kper outages), found by a
+  // reciprocal (slots are below 2^15)
+  const int kper = lay.k3_kper, spr = (kper + 1) / 2;
+  const int np = SWEEP && net.K > 0 ? (net.K + kper - 1) / kper * spr : 0;
+  const int per = T / Lp4, col = tid % Lp4, t0 = tid / Lp4 < per ? tid / Lp4 : np;
+  const float inv = 1.0f / (float)spr;
+  auto slot = [&](int t, int& row, int& i) {
+    row = (int)(((float)t + 0.5f) * inv);
+    i = 2 * (t - row * spr);
+  };
+  const float4* lam = reinterpret_cast<const float4*>(net.lodf) + col;
+  auto factors = [&](int t, float4& x0, float4& x1) {
+    int row, i;
+    slot(t, row, i);
+    const int k = min(row * kper + i, net.K - 1);
+    x0 = lam[(size_t)k * Lp4];
+    x1 = lam[(size_t)min(k + 1, net.K - 1) * Lp4];
+  };
   constexpr int kAhead = 2;
   float4 xa[kAhead], xb[kAhead];
-  auto load_items = [&](int i0) {
+  auto load_items = [&](int t) {
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int it = i0 + u * T;
-      if (it < np * Lp4) {
-        const int col = it % Lp4, k = 2 * (it / Lp4);
-        xa[u] = lam[(size_t)k * Lp4 + col];
-        xb[u] = lam[(size_t)(k + 1) * Lp4 + col];
-      }
-    }
+    for (int u = 0; u < kAhead; ++u)
+      if (t + u * per < np) factors(t + u * per, xa[u], xb[u]);
   };
-  if (WIDE && SWEEP) load_items(tid);
+  if (WIDE && SWEEP) load_items(t0);
   const float* lo = box_lo + b * net.X;
   const float* hi = box_hi + b * net.X;
   // line constants of this thread's first line, loaded with the box
@@ -877,53 +891,58 @@ __global__ __launch_bounds__(T) void km_box(DevNet net, const float* __restrict_
   if (!SWEEP) return;
 
   double acc_hi = 0.0, acc_lo = 0.0;
-  auto column = [&](int col, float4& c4, float4& h4, float4& g4) {
+  if (t0 < np) {
     const float4 e4 = reinterpret_cast<const float4*>(net.line_eps)[col];
-    c4 = make_float4(s_lc[4 * col], s_lc[4 * col + 1], s_lc[4 * col + 2], s_lc[4 * col + 3]);
-    h4 = make_float4(add_ru(s_lh[4 * col], next_up_f32(e4.x * vmax)), add_ru(s_lh[4 * col + 1], next_up_f32(e4.y * vmax)),
-                     add_ru(s_lh[4 * col + 2], next_up_f32(e4.z * vmax)), add_ru(s_lh[4 * col + 3], next_up_f32(e4.w * vmax)));
-    g4 = make_float4(add_ru(s_lg[4 * col], next_up_f32(e4.x * vmax)), add_ru(s_lg[4 * col + 1], next_up_f32(e4.y * vmax)),
-                     add_ru(s_lg[4 * col + 2], next_up_f32(e4.z * vmax)), add_ru(s_lg[4 * col + 3], next_up_f32(e4.w * vmax)));
-  };
-  auto item = [&](int it, const float4& x0, const float4& x1) {
-    const int col = it % Lp4, k = 2 * (it / Lp4);
-    float4 c4, h4, g4;
-    column(col, c4, h4, g4);
-    k3_pair(x0, s_ctg[k], x1, s_ctg[k + 1], c4, h4, g4, acc_hi, acc_lo);
-  };
-  if constexpr (WIDE) {
-    for (int i0 = tid; i0 < np * Lp4; i0 += kAhead * T) {
-      float4 x0[kAhead], x1[kAhead];
-#pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        x0[u] = xa[u];
-        x1[u] = xb[u];
+    const float ex = next_up_f32(e4.x * vmax), ey = next_up_f32(e4.y * vmax);
+    const float ez = next_up_f32(e4.z * vmax), ew = next_up_f32(e4.w * vmax);
+    const int l = 4 * col;
+    const float4 c4 = make_float4(s_lc[l], s_lc[l + 1], s_lc[l + 2], s_lc[l + 3]);
+    const float4 h4 = make_float4(add_ru(s_lh[l], ex), add_ru(s_lh[l + 1], ey), add_ru(s_lh[l + 2], ez), add_ru(s_lh[l + 3], ew));
+    const float4 g4 = make_float4(add_ru(s_lg[l], ex), add_ru(s_lg[l + 1], ey), add_ru(s_lg[l + 2], ez), add_ru(s_lg[l + 3], ew));
+    // two outages' penalties of four lines: one float32 sum of eight where the other
+    // sweeps pair them, two of four at a row's end
+    auto item = [&](int t, const float4& x0, const float4& x1) {
+      int row, i;
+      slot(t, row, i);
+      const int k = row * kper + i, len = min(kper, net.K - row * kper);
+      if (i >= len) return;
+      const int4 d0 = s_ctg[k], d1 = s_ctg[min(k + 1, net.K - 1)];
+      if (i + 2 <= (len & -lay.k3_unit)) {  // (k3_unit is 2 or 4)
+        k3_pair(x0, d0, x1, d1, c4, h4, g4, acc_hi, acc_lo);
+        return;
       }
-      load_items(i0 + kAhead * T);
+      auto one = [&](const float4& x, const int4& d) {
+        const float cc = __int_as_float(d.y), rk = __int_as_float(d.z);
+        float a0, a1, a2, a3, q0a, q1, q2, q3;
+        k3_elem(x.x, cc, rk, c4.x, h4.x, g4.x, a0, q0a);
+        k3_elem(x.y, cc, rk, c4.y, h4.y, g4.y, a1, q1);
+        k3_elem(x.z, cc, rk, c4.z, h4.z, g4.z, a2, q2);
+        k3_elem(x.w, cc, rk, c4.w, h4.w, g4.w, a3, q3);
+        acc_hi += (double)((a0 + a1) + (a2 + a3));
+        acc_lo += (double)((q0a + q1) + (q2 + q3));
+      };
+      one(x0, d0);
+      if (i + 1 < len) one(x1, d1);
+    };
+    if constexpr (WIDE) {
+      for (int t = t0; t < np; t += kAhead * per) {
+        float4 x0[kAhead], x1[kAhead];
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u)
-        if (i0 + u * T < np * Lp4) item(i0 + u * T, x0[u], x1[u]);
-    }
-  } else {
-    for (int it = tid; it < np * Lp4; it += T) {
-      const int col = it % Lp4, k = 2 * (it / Lp4);
-      item(it, lam[(size_t)k * Lp4 + col], lam[(size_t)(k + 1) * Lp4 + col]);
-    }
-  }
-  if (net.K & 1) {  // the last outage of an odd count, alone
-    const int k = net.K - 1;
-    for (int col = tid; col < Lp4; col += T) {
-      const float4 x0 = lam[(size_t)k * Lp4 + col];
-      float4 c4, h4, g4;
-      column(col, c4, h4, g4);
-      const float cc0 = __int_as_float(s_ctg[k].y), rk0 = __int_as_float(s_ctg[k].z);
-      float a0, a1, a2, a3, q0a, q1, q2, q3;
-      k3_elem(x0.x, cc0, rk0, c4.x, h4.x, g4.x, a0, q0a);
-      k3_elem(x0.y, cc0, rk0, c4.y, h4.y, g4.y, a1, q1);
-      k3_elem(x0.z, cc0, rk0, c4.z, h4.z, g4.z, a2, q2);
-      k3_elem(x0.w, cc0, rk0, c4.w, h4.w, g4.w, a3, q3);
-      acc_hi += (double)((a0 + a1) + (a2 + a3));
-      acc_lo += (double)((q0a + q1) + (q2 + q3));
+        for (int u = 0; u < kAhead; ++u) {
+          x0[u] = xa[u];
+          x1[u] = xb[u];
+        }
+        load_items(t + kAhead * per);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+          if (t + u * per < np) item(t + u * per, x0[u], x1[u]);
+      }
+    } else {
+      for (int t = t0; t < np; t += per) {
+        float4 x0, x1;
+        factors(t, x0, x1);
+        item(t, x0, x1);
+      }
     }
   }
   acc_hi = wave_sum(acc_hi);
@@ -972,7 +991,8 @@ void plan_single(const DevNet& net, int64_t n_box, WsLayout& lay, const Tune& t)
   lay.k2_nc = t.k2_nc;
   lay.k3_kc = t.k3_kc;
   // the smallest networks: one launch, one block per box (km_box)
-  lay.small = net.N <= kMicroBuses && net.L <= kMicroLines && (int64_t)net.K * net.Lp <= kMicroElems;
+  lay.small = micro_net(net);
+  lay.k3_kper = net.K;
   lay.n_p1 = lay.small ? 1 : (std::max(net.Np, net.X) + 63) / 64;
   lay.k2_bx = (lp4 + 63) / 64;
   lay.k2_by = std::max(1, (net.N + 4 * t.k2_nc - 1) / (4 * t.k2_nc));
@@ -983,6 +1003,12 @@ void plan_single(const DevNet& net, int64_t n_box, WsLayout& lay, const Tune& t)
   lay.n_p3 = net.K > 0 ? lay.k3_bx * lay.k3_by : 0;
   if (lay.small) lay.n_p2 = lay.n_p3 = 1;
 }
+
+// One block per box pays for as many boxes as run side by side, against five launches of
+// the box-tiled path (35 to 55 us): 512 boxes at 40 buses 55 -> 16 us, 2048 56 -> 36;
+// wide blocks, one per CU, 256 boxes at 160 buses 42 -> 24 us, 4 boxes 38 -> 21 (512
+// boxes at 160 buses 45, one block each 49 before the columns).
+bool micro_pays(const DevNet& net, int64_t n_box) { return micro_net(net) && n_box <= (micro_wide(net) ? 256 : 2048); }
 
 template <int NC>
 static void launch_k2(const DevNet& net, void* ws, const WsLayout& lay, int64_t b0, int nb, hipStream_t s,

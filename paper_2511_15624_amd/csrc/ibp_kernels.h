@@ -60,6 +60,7 @@ struct Tune {
   int k5_sparse = 1; // box-tiled gradient of f_hi: screened sweep over candidate lines (0: dense sweep)
   int k3_sparse = 1; // box-tiled one-sided forward: screened sweep over candidate lines (0: dense sweep)
   int k3_lin = -1;   // box-tiled forward: linear sweep 0 off, 1 wherever it fits, -1 by size (needs k3_sparse)
+  int micro = 1;     // small networks: several boxes, one block each (0: box-tiled)
   int k3_scr = 0;    // box-tiled calls bounding f_lo screen the upper penalties (as IBP_F_SCREEN_UPPER)
 };
 
@@ -130,6 +131,8 @@ int batched_rows_rule(const DevNet& net, int k3_bx, int64_t groups);
 
 // Grid shapes and partial-sum counts of the single-box-per-slice forward path.
 void plan_single(const DevNet& net, int64_t n_box, WsLayout& lay, const Tune& t);
+// Whether `n_box` boxes of a small network take one block each (two-sided bounds).
+bool micro_pays(const DevNet& net, int64_t n_box);
 
 // Box-tiled plan (n_box >= kBatchMin and no IBP_F_PLAIN).
 void plan_batched(const DevNet& net, int64_t n_box, WsLayout& lay, const Tune& t);
