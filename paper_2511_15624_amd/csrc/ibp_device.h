@@ -91,9 +91,9 @@ struct FwdLayout {
   int k2_by = 0;                   // bus chunks of the base flows (K2 grid per box: line tiles x bus chunks)
   int k2_chunk = 0;                // batched base flows: buses per chunk (k2_by chunks, a multiple of 4)
   int k3_kper = 0;                 // batched outage sweep (and one block per box): outages per row
-  int k3_unit = 2;                 // one block per box: outages of a row pair up to the last multiple of this many
-  int k3_xcd = 0;                  // box-tiled outage sweep in XCD-aware block order
-  int sides = 3;                   // penalty sides of the outage sweep: 3 both, 1 lower (f_hi), 2 upper (f_lo)
+  int8_t k3_unit = 2;              // one block per box: outages of a row pair up to the last multiple of this many
+  int8_t k3_xcd = 0;               // box-tiled outage sweep in XCD-aware block order
+  int8_t sides = 3;                // penalty sides of the outage sweep: 3 both, 1 lower (f_hi), 2 upper (f_lo)
 };
 
 struct WsLayout : FwdLayout {

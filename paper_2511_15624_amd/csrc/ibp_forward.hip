@@ -748,17 +748,28 @@ __global__ __launch_bounds__(T) void km_box(DevNet net, const float* __restrict_
   };
   if constexpr (WIDE) load_rows(0);
   // outage sweep: a thread has one column of four lines and every per-th slot of two
-  // outages; slot t is the (t % spr)-th of row t / spr (kper outages), found by a
-  // reciprocal (slots are below 2^15)
-  const int kper = lay.k3_kper, spr = (kper + 1) / 2;
-  const int np = SWEEP && net.K > 0 ? (net.K + kper - 1) / kper * spr : 0;
-  const int per = T / Lp4, col = tid % Lp4, t0 = tid / Lp4 < per ? tid / Lp4 : np;
-  const float inv = 1.0f / (float)spr;
+  // outages; slot t is the (t % spr)-th of row t / spr (kper outages).  Quotients by a
+  // reciprocal: below 2^15, a half away from the next integer
+  auto quotient = [](int a, float inv) { return (int)(((float)a + 0.5f) * inv); };
+  const int kper = lay.k3_kper;
+  int spr = 0, np = 0, per = 0, col = 0, t0 = 0;
+  float inv = 0.0f;
+  const float4* lam = nullptr;
+  auto plan_sweep = [&] {
+    spr = (kper + 1) / 2;
+    inv = __builtin_amdgcn_rcpf((float)spr);
+    const float inv4 = __builtin_amdgcn_rcpf((float)Lp4);
+    np = net.K > 0 ? quotient(net.K + kper - 1, __builtin_amdgcn_rcpf((float)kper)) * spr : 0;
+    per = quotient(T, inv4);
+    const int first = quotient(tid, inv4);
+    col = tid - first * Lp4;
+    t0 = first < per ? first : np;
+    lam = reinterpret_cast<const float4*>(net.lodf) + col;
+  };
   auto slot = [&](int t, int& row, int& i) {
-    row = (int)(((float)t + 0.5f) * inv);
+    row = quotient(t, inv);
     i = 2 * (t - row * spr);
   };
-  const float4* lam = reinterpret_cast<const float4*>(net.lodf) + col;
   auto factors = [&](int t, float4& x0, float4& x1) {
     int row, i;
     slot(t, row, i);
@@ -773,7 +784,10 @@ __global__ __launch_bounds__(T) void km_box(DevNet net, const float* __restrict_
     for (int u = 0; u < kAhead; ++u)
       if (t + u * per < np) factors(t + u * per, xa[u], xb[u]);
   };
-  if (WIDE && SWEEP) load_items(t0);
+  if (WIDE && SWEEP) {
+    plan_sweep();
+    load_items(t0);
+  }
   const float* lo = box_lo + b * net.X;
   const float* hi = box_hi + b * net.X;
   // line constants of this thread's first line, loaded with the box
@@ -891,6 +905,7 @@ __global__ __launch_bounds__(T) void km_box(DevNet net, const float* __restrict_
   if (!SWEEP) return;
 
   double acc_hi = 0.0, acc_lo = 0.0;
+  if (!WIDE) plan_sweep();
   if (t0 < np) {
     const float4 e4 = reinterpret_cast<const float4*>(net.line_eps)[col];
     const float ex = next_up_f32(e4.x * vmax), ey = next_up_f32(e4.y * vmax);
