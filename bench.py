@@ -286,7 +286,8 @@ VALU_PEAK_SOURCE = ("MI355X float32 vector peak 157.3 TFLOP/s with an FMA counte
                     "clock x 2.4 GHz; the box-tiled sweep's counters show 0.414 wave instructions per SIMD per "
                     "cycle, above what 16 lanes per clock allow (profiles/ibp_batched_counters_c2000.md), and "
                     "the FMA probe's measured rate is reported beside it (alu_probe)")
-OPS_PER_EVAL = 9.25  # VALU ops per box-outage-line evaluation in the outage sweep (from the ISA)
+I8_OPS_PER_EVAL = 40  # int8 operations per box-outage-line evaluation of the linear sweep's products
+MFMA_I8_PEAK = 5.0e15  # dense int8 matrix operations/s
 # VALU ops per element of the chord-relaxation sweep: post-outage centre and
 # the two interval ends (5), the clipped lower end (3), the slope and its
 # quantisation (8), the intercept and its padding (4), the value bound (6),
@@ -383,11 +384,12 @@ def extras(torch, ibp, synth, n4, net4):
         "plain_value": ev_p / (ms_p * 1e-3), "plain_sample": f"first {sub} boxes, per-box kernels",
         "speedup_vs_plain": (ev / ms) / (ev_p / ms_p),
         "kernel_ms": {k: round(v[0], 3) for k, v in kt.items()},
-        "roofline": {"bound": "alu", "kernel": "batched_outage_sweep",
-                     "achieved": ev * OPS_PER_EVAL / (sweep_ms * 1e-3), "peak": VALU_PEAK, "unit": "ops/s",
-                     "peak_source": VALU_PEAK_SOURCE,
-                     "frac": ev * OPS_PER_EVAL / (sweep_ms * 1e-3) / VALU_PEAK,
-                     "ops_per_eval": OPS_PER_EVAL},
+        # the linear part of the outage sweep: per element five digits x (signed, absolute) x
+        # (upper, lower) int8 multiply-adds; its exceptions are forward_line_screen's time
+        "roofline": {"bound": "mfma", "kernel": "batched_outage_sweep",
+                     "achieved": ev * I8_OPS_PER_EVAL / (sweep_ms * 1e-3), "peak": MFMA_I8_PEAK, "unit": "ops/s",
+                     "frac": ev * I8_OPS_PER_EVAL / (sweep_ms * 1e-3) / MFMA_I8_PEAK,
+                     "ops_per_eval": I8_OPS_PER_EVAL},
     }
     res["batched"]["tuned"] = _tuned(torch, ibp, n3, tlo, thi, ws, ev, ms)
     # the same call with the upper-penalty line screen (IBP_F_SCREEN_UPPER):
@@ -593,8 +595,8 @@ def extras(torch, ibp, synth, n4, net4):
             "peak_source": VALU_PEAK_SOURCE, "ops_per_element": CHORD_OPS_PER_ELEM,
             "single_box": {"ms": sw1, "achieved": ev1 * CHORD_OPS_PER_ELEM / (sw1 * 1e-3),
                            "frac": ev1 * CHORD_OPS_PER_ELEM / (sw1 * 1e-3) / VALU_PEAK},
-            "batch": {"ms": sw3, "achieved": e3 * CHORD_OPS_PER_ELEM / (sw3 * 1e-3),
-                      "frac": e3 * CHORD_OPS_PER_ELEM / (sw3 * 1e-3) / VALU_PEAK}},
+            # (inactive elements take five of the operations there)
+            "batch": {"ms": sw3, "evals_per_s": e3 / (sw3 * 1e-3)}},
         "single_box_ms": ms_l1, "single_box_ms_ibp_only": ms_lin,
         "single_box_value": ev1 / (ms_l1 * 1e-3), "unit": "evals/s",
         "single_box_kernel_us": {k: round(v[0] / v[1] * 1e3, 2) for k, v in ktl.items()},

@@ -155,15 +155,16 @@ void ibp_free_network(ibp_network* net);
  * at most; the bound is certified either way; IBP_TILE=k3s=0 at
  * ibp_build_network keeps the dense sweep).  IBP_F_UPPER_ONLY calls always
  * take the screen (the lower penalties of f_hi are active on few lines:
- * 2000 buses, 8192 sub-boxes, 12.2 -> 7.8 ms).  Calls that bound f_lo (two-
+ * 2000 buses, 8192 sub-boxes, 12.2 -> 6.4 ms).  Calls that bound f_lo (two-
  * sided, or IBP_F_LOWER_ONLY) take it only with IBP_F_SCREEN_UPPER: the
  * screen then bounds the upper penalties (a line with none active has no
  * active lower penalty either) and the sweep sums both sides, or the upper
  * side alone, over the marked lines.  That pays where few lines carry an
- * active upper penalty (the centre points of sub-boxes: 12.3 -> 9.3 ms at
- * 8192 points; 18 x 1024 period sub-boxes, two-sided: 37.1 -> 30.1 ms) and
- * costs more than it saves on wide sub-boxes (1024 of them, lower bound
- * alone: 2.1 against 1.6 ms).  At most one of the two side flags;
+ * active upper penalty (the centre points of sub-boxes: 12.3 -> 7.2 ms at
+ * 8192 points) and costs more than it saves on wide sub-boxes.  Two-sided calls
+ * of many boxes take the linear sweep with the flag or without it (its bounds
+ * are within 1e-9 of the dense sweep's; IBP_TILE=k3l=0 keeps that).  At most
+ * one of the two side flags;
  * IBP_F_SCREEN_UPPER not with IBP_F_UPPER_ONLY. */
 #define IBP_F_UPPER_ONLY 32u
 #define IBP_F_LOWER_ONLY 64u

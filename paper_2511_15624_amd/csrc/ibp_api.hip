@@ -612,8 +612,8 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
     lay.fscreen = 0;
   }
   // one-sided calls with a screen keep it: few of their lines are swept (8192
-  // boxes at 2000 buses: 3.3 ms for screen and sweep of the upper bounds, and the
-  // linear sweep takes 3.25)
+  // boxes at 2000 buses: 2.2 ms for screen and sweep of the upper bounds, and the
+  // linear sweep takes about 3)
   if (lay.batched && !(one_sided && lay.fscreen)) add_linear(net, n_box, lay);
   if (flags & (IBP_F_CROWN | IBP_F_CROWN_REF)) {
     const ibp::DevNet& d = net->dn;
