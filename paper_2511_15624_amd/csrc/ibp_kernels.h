@@ -110,7 +110,7 @@ constexpr int kLinLines = 32;
 constexpr int kLinDigits = 5;
 constexpr float kLinMaxFactor = 1.9f;
 inline int lin_ktiles(int K) { return (K + 31) / 32; }
-inline int lin_pair_chunks(int K) { return (K + 1023) / 1024; }
+inline int lin_pair_chunks(int K) { return (K + 2047) / 2048; }
 constexpr int kHeavyLines = 128, kHeavyK = 512;
 inline int lin_heavy_tiles(int Lp) { return (Lp + kHeavyLines - 1) / kHeavyLines; }
 inline int lin_heavy_chunks(int K) { return (K + kHeavyK - 1) / kHeavyK; }
