@@ -1016,7 +1016,7 @@ void plan_single(const DevNet& net, int64_t n_box, WsLayout& lay, const Tune& t)
   lay.k3_bx = (lp4 + 255) / 256;
   lay.k3_by = std::max(1, (net.K + t.k3_kc - 1) / t.k3_kc);
   lay.n_p3 = net.K > 0 ? lay.k3_bx * lay.k3_by : 0;
-  if (lay.small) lay.n_p2 = lay.n_p3 = 1;
+  if (lay.small) lay.k2_by = lay.n_p2 = lay.n_p3 = 1;
 }
 
 // One block per box pays for as many boxes as run side by side, against five launches of
