@@ -569,7 +569,7 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
   // rounding is the same there.
   const ibp::Tune& tune = net->tune;
   const bool micro = (flags & ~uint32_t(IBP_F_CROWN | IBP_F_CROWN_REF)) == 0 && batched && tune.micro &&
-                     tune.k2b_mfma && tune.k2_by == 0 && !tune.k3_scr && tune.k3_lin != 1 &&
+                     tune.k2b_mfma && tune.k2_by <= 1 && !tune.k3_scr && tune.k3_lin != 1 &&
                      ibp::micro_pays(net->dn, n_box);
   ibp::WsLayout lay = layout_for(net, n_box, net->tune, batched && !micro);
   if (micro) {
