@@ -330,11 +330,13 @@ __global__ __launch_bounds__(256, 4) void kn_lines(DevNet net, void* ws, WsLayou
       if (lane == 0) ws_ptr<uint64_t>(ws, lay.nk)[(size_t)g * net.Lp + l] = nm;
       const bool on = !hv && !near;
       lin |= (on ? 1u : 0u) << j;
-      const double n = l < net.L ? (double)(net.K - (net.ctg_of_line[l] >= 0)) : 0.0;
+      const bool own = l < net.L && net.ctg_of_line[l] >= 0;  // the line's own outage has no element of it
+      const double n = l < net.L ? (double)(net.K - own) : 0.0;
       const unsigned sgn = c[j] < 0.0f ? 0xffu : 1u;
-      // A line that no outage moves (a bridge, which is never an outage) has the
-      // same float32 element x or y for all of them in the dense sweep, and so has
-      // a quad of such lines its sum: their rounding is taken as it is there.
+      // A line that no other outage moves (a bridge, or a line of a loop of which no
+      // other line is studied) has the same float32 element x or y for all of them in
+      // the dense sweep: its rounding is taken as it is there, and so is that of a
+      // quad's sum, where every active line of it is such a line and a bridge (n = K).
       const bool rigid = net.lam_max[l] * wmax < 0x1p-26f * ac;
       if ((j & 3) == 0) {
         th_hi = th_lo = 0.0;
@@ -346,14 +348,14 @@ __global__ __launch_bounds__(256, 4) void kn_lines(DevNet net, void* ws, WsLayou
         th_hi += n * (rigid ? (double)x : (double)ac + (double)h[j]);
         e_hi += n * ((double)ac + fabs((double)h[j]));
         vu[j >> 2] |= sgn << (8 * (j & 3));
-        all_hi &= rigid;
+        all_hi &= rigid && !own;
       }
       if (LO && on && y > 0.0f) {
         py = y;
         th_lo += n * (rigid ? (double)y : (double)ac - (double)q[j]);
         e_lo += n * ((double)ac + (double)q[j]);
         vl[j >> 2] |= sgn << (8 * (j & 3));
-        all_lo &= rigid;
+        all_lo &= rigid && !own;
       }
       // the dense sweep's order: (l0 + l1) + (l2 + l3)
       if (j & 1) {
