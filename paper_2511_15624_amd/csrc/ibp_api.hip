@@ -303,12 +303,12 @@ ibp_status to_device(ibp_network* net, int device) {
     if ((st = upload(net, lt.data(), lt.size(), &d.lodfT)) != IBP_OK) return st;
     if ((st = upload(net, amax.data(), amax.size(), &d.lam_max)) != IBP_OK) return st;
     // digit planes of the linear sweep, made on the device from the uploaded
-    // factors; without them (no memory, or a factor they cannot hold) the
-    // dense sweep serves
+    // factors; without them (no memory, a factor they cannot hold, or more lines
+    // than their sums hold) the dense sweep serves
     d.lin_dig = d.lin_dga = nullptr;
     const char* tile = std::getenv("IBP_TILE");
     const bool wanted = (int64_t)h.K * h.L >= kLinMinElems || (h.K > 0 && tile && std::strstr(tile, "k3l=1"));
-    if (wanted && *std::max_element(amax.begin(), amax.end()) < ibp::kLinMaxFactor) {
+    if (wanted && h.L <= ibp::kLinMaxLines && *std::max_element(amax.begin(), amax.end()) < ibp::kLinMaxFactor) {
       void* p = nullptr;
       const size_t bytes = ibp::lin_digit_bytes(d), all = 2 * bytes + (size_t)d.Lp * 64 * sizeof(float);
       if (hipMalloc(&p, all) == hipSuccess) {

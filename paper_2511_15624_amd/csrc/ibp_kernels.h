@@ -104,11 +104,15 @@ void launch_line_screen(const DevNet& net, int64_t n_box, void* ws, const WsLayo
 void launch_screened_forward_sweep(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay, int sides,
                                    hipStream_t s);
 // Linear outage sweep (see ibp_linear.hip): boxes per group (a lane each), lines
-// per block, digits of a factor, and the largest factor the digits hold.
+// per block, digits of a factor, the largest factor the digits hold, and the most
+// lines over which the sums of two digits (-128 to 127) join in an int32:
+// 128 (256 + 1) L < 2^31.
 constexpr int kLinGroup = 64;
 constexpr int kLinLines = 32;
 constexpr int kLinDigits = 5;
 constexpr float kLinMaxFactor = 1.9f;
+constexpr int kLinMaxLines = 65280;
+static_assert(128ll * 257 * kLinMaxLines < (1ll << 31) && 128ll * 257 * (kLinMaxLines + 1) >= (1ll << 31));
 inline int lin_ktiles(int K) { return (K + 31) / 32; }
 inline int lin_pair_chunks(int K) { return (K + 2047) / 2048; }
 constexpr int kHeavyLines = 128, kHeavyK = 512;

@@ -803,7 +803,7 @@ __global__ __launch_bounds__(64 * MW * NW) void kn_gemm(DevNet net, void* ws, Ws
     for (int r = 0; r < 16; ++r) {
       const int k = kt * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
       const float2 o = oc[(size_t)min(k, net.K - 1) * kLinGroup];  // rows past the last outage have zero digits
-      // digit sums are below 127 L, so two of them join in 32 bits
+      // a digit sum is at most 128 L, so two of them join in 32 bits up to kLinMaxLines lines
       const int y01 = acc[1][j][r] * 256 + acc[0][j][r], y23 = acc[3][j][r] * 256 + acc[2][j][r];
       const double y = fma((double)acc[4][j][r], 0x1p-6, fma((double)y23, 0x1p-22, (double)y01 * 0x1p-38));
       if (abs_) {

@@ -1,10 +1,12 @@
 """The linear outage sweep where a chosen set of outages is studied (``ctg_line``
-given): loops of which one line alone is an outage.  No other outage moves that line,
-and its own outage has no element of it, so it is summed over one outage fewer than a
-bridge is.
+given).
 
-Only such lines are overloaded here, so one element too many or too few is far above the
-box's error budget on either side."""
+Loops of which one line alone is an outage: no other outage moves that line, and its own
+outage has no element of it, so it is summed over one outage fewer than a bridge is.
+Only such lines are overloaded, so one element too many or too few is far above the
+box's error budget on either side.
+
+More lines than the int32 sums of two digits hold: the dense sweep serves."""
 import numpy as np
 import pytest
 
@@ -76,9 +78,43 @@ def test_a_line_counts_in_no_outage_of_its_own(monkeypatch, loop, count):
     tlo, thi = torch.from_numpy(lo).cuda(), torch.from_numpy(hi).cuda()
     (f_lo, f_hi), linear = runs_linear(n, lambda: ibp.ibp_bound_boxes(n, tlo, thi))
     assert linear
-    f_lo, f_hi = f_lo.cpu().numpy(), f_hi.cpu().numpy()
-    for b in (0, 31, 63):
+    _within_budget(net, fac, n, lo, hi, f_lo.cpu().numpy(), f_hi.cpu().numpy(), (0, 31, 63))
+    n.close()
+
+
+def _within_budget(net, fac, n, lo, hi, f_lo, f_hi, sample):
+    for b in sample:
         bu = budget(net, fac, lo[b], hi[b], n.info.phi_abs_err)
         assert 0.0 <= bu["r"]["f_lo"] - f_lo[b] <= bu["lo"], (b, bu["r"]["f_lo"] - f_lo[b], bu["lo"])
         assert 0.0 <= f_hi[b] - bu["r"]["f_hi"] <= bu["hi"], (b, f_hi[b] - bu["r"]["f_hi"], bu["hi"])
+
+
+def test_more_lines_than_the_digit_sums_hold(monkeypatch):
+    """A chain of 520 stages of 130 equal circuits, all overloaded, and two weak lines
+    across it, the outages: each moves its flow onto 67600 lines by about 1/130 = 32264 /
+    2^22 apiece, whose two middle digits add up to 67600 * 32264 > 2^31."""
+    import torch
+    stages, m = 520, 130
+    fr = np.concatenate([np.repeat(np.arange(stages), m), [0, 0]]).astype(np.int32)
+    to = np.concatenate([np.repeat(np.arange(1, stages + 1), m), [stages, stages]]).astype(np.int32)
+    L = fr.size
+    net = dict(n_bus=stages + 1, slack_bus=0, line_from=fr, line_to=to,
+               line_b=np.concatenate([np.full(L - 2, 20.0), [2e-3, 1e-3]]),
+               gen_bus=np.array([0, 0], np.int32), gen_cost=np.array([20.0, 30.0]), gen_pmin=np.array([0.2, 0.0]),
+               gen_pmax=np.array([2.0, 1.0]), load_bus=np.full(3, stages, np.int32),
+               load_value=np.array([80.0, 90.0, 70.0]), load_dmin=np.array([0.4, 0.5, 0.6]),
+               load_dmax=np.array([0.5, 0.6, 0.7]), zeta_inj=1e3, zeta_f=5e2,
+               ctg_line=np.array([L - 2, L - 1], np.int32))
+    net["fmax_base"] = np.full(L, 0.5 * 1.65 / m)
+    net["fmax_ctg"] = net["fmax_base"]
+    fac = oracle.factors(net)
+    monkeypatch.setenv("IBP_TILE", "k3l=1")
+    n = ibp.Network(net, device=0)
+    monkeypatch.delenv("IBP_TILE")
+    print(f"[digit sums] {n.n_line} lines, {n.n_ctg} outages", flush=True)
+    lo, hi = synth.sub_boxes(net, 64, seed=3)
+    tlo, thi = torch.from_numpy(lo).cuda(), torch.from_numpy(hi).cuda()
+    (f_lo, f_hi), linear = runs_linear(n, lambda: ibp.ibp_bound_boxes(n, tlo, thi))
+    _within_budget(net, fac, n, lo, hi, f_lo.cpu().numpy(), f_hi.cpu().numpy(), (0, 40))
+    assert not linear
     n.close()
