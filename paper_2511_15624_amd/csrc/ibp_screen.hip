@@ -96,14 +96,15 @@ __device__ __forceinline__ float line_g(const DevNet& net, void* ws, const WsLay
   return add_ru(ws_ptr<float>(ws, lay.lg)[b * net.Lp + l], next_up_f32(net.line_eps[l] * vmax));
 }
 
-// K5w: per tile and outage W (zero past the last outage); per tile and block
-// of 256 outages the largest |c_c| + r_c, for the margin.
+// K5w: per tile (grid x: a call may have more than the 65535 of the other two) and
+// outage W (zero past the last outage); per tile and block of 256 outages the largest
+// |c_c| + r_c, for the margin.
 template <int MODE>
 __global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
   constexpr int S = kScreenBoxes;
   __shared__ unsigned zs[4];
-  const int k = blockIdx.x * 256 + threadIdx.x;
-  const int64_t t = blockIdx.y;
+  const int k = blockIdx.y * 256 + threadIdx.x;
+  const int64_t t = blockIdx.x;
   float wv = 0.0f, z = 0.0f;
   if (k < net.K) {
 #pragma unroll
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(256) void k5w_tile_max(DevNet net, void* ws, WsLayo
   if ((threadIdx.x & 63) == 0) zs[threadIdx.x >> 6] = zb;
   __syncthreads();
   if (threadIdx.x == 0)
-    ws_ptr<float>(ws, lay.sz)[t * lay.k5w_bx + blockIdx.x] =
+    ws_ptr<float>(ws, lay.sz)[t * lay.k5w_bx + blockIdx.y] =
         __uint_as_float(max(max(zs[0], zs[1]), max(zs[2], zs[3])));
 }
 
@@ -290,12 +291,13 @@ static void launch_screen_mode(const DevNet& net, int64_t n_box, void* ws, const
   const int group = 256 << lay.cm_shift;
   const int k_per = ((net.K + z - 1) / z + group - 1) / group * group;
   const unsigned gx = (net.Lp + 255) / 256, gz = (unsigned)((net.K + k_per - 1) / k_per);
-  hipLaunchKernelGGL(k5w_tile_max<MODE>, dim3(lay.k5w_bx, lay.k5s_tiles), dim3(256), 0, s, net, ws, lay, n_box);
+  hipLaunchKernelGGL(k5w_tile_max<MODE>, dim3(lay.k5s_tiles, lay.k5w_bx), dim3(256), 0, s, net, ws, lay, n_box);
   const dim3 grid(gx, (lay.k5s_tiles + g - 1) / g, gz);
   if (g == 16)
     hipLaunchKernelGGL((k5s_screen<MODE, 16>), grid, dim3(256), 0, s, net, ws, lay, n_box, k_per);
   else
     hipLaunchKernelGGL((k5s_screen<MODE, 4>), grid, dim3(256), 0, s, net, ws, lay, n_box, k_per);
+  // (a split screen has at most kScreenBlocks / 2 tile groups: far below 65535 rows)
   if (gz > 1) hipLaunchKernelGGL(k5s_mark<MODE>, dim3(gx, lay.k5s_tiles), dim3(256), 0, s, net, ws, lay, n_box);
 }
 
