@@ -152,21 +152,30 @@ ibp_status scratch_address(int device, void** out) {
   return IBP_OK;
 }
 
-// Where the linear sweep takes over from the dense and screened ones (k3_lin = -1).
-// Its scan costs the same for 1 and 64 boxes and its operands are padded to 64,
-// so it needs many boxes: 2000 buses, both bounds: 256 boxes 614 against 628 us,
-// 512 945 against 1143, 1024 1.47 against 2.13 ms; 4000 buses 128 boxes 1194
-// against 1059 us, 256 1577 against 2000; 8316 buses 64 boxes 1731 against 1771,
-// 128 2.49 against 3.31 ms; 1000 buses 1024 boxes 625 against 641 us, 4096 1.91
-// against 2.31 ms.  Below kLinMinElems elements the two sweeps' bounds differ by up
-// to 1e-9 (few lines carry the sum, and their float32 units differ).
+// Where the linear sweep takes over from the dense one (k3_lin = -1).  Its scan costs the
+// same for 1 and 64 boxes, its operands are padded to 64, and it sums both sides at
+// little more than the cost of one, so it needs many elements, many boxes, and more of
+// both for one side (f_lo alone; f_hi alone takes the screen).  Narrow boxes leave fewer
+// exceptions than wide ones; the lines lie between the two kinds.  Linear over dense,
+// sub-boxes / whole boxes, at K L elements and boxes:
+//   both bounds  4.8M: 1024 0.98 / 1.10, 2048 0.87 / 0.98;  9.4M: 256 1.03 / 1.26,
+//     512 0.81 / 0.95;  14.5M: 256 0.98 / 1.12, 512 0.77 / 0.89;  18.3M: 192 1.02, 256
+//     0.91 / 0.99;  37.9M: 128 1.07 / 1.20, 256 0.77 / 0.86;  112M: 96 0.90, 128 0.75 / 0.80
+//   f_lo alone  2.5M: 4096 1.10 / 1.26;  4.8M: 2048 1.02 / 1.14, 4096 0.92 / 1.04;  9.4M:
+//     512 0.94 / 1.06, 1024 0.87 / 0.99;  14.5M: 512 0.90 / 0.99;  18.3M: 512 0.92 / 0.96;
+//     37.9M: 256 0.89 / 1.00;  112M: 96 1.01, 128 0.87 / 0.92
+// Below kLinMinElems elements the two sweeps' bounds differ by up to 1e-9 (few
+// lines carry the sum, and their float32 units differ).
 constexpr int64_t kLinMinElems = 2500000;  // outages x lines
-constexpr int64_t kLinMinWork = 3000000000ll;  // x boxes
-constexpr int64_t kLinMinBoxes = 192, kLinMinBoxesLarge = 96, kLinLarge = 80000000;
+constexpr int64_t kLinMinElemsOne = 4000000;
 
-bool linear_pays(const ibp::DevNet& d, int64_t n_box) {
+bool linear_pays(const ibp::DevNet& d, int64_t n_box, bool one_sided) {
   const int64_t e = (int64_t)d.K * d.L;
-  return e >= kLinMinElems && e * n_box >= kLinMinWork && n_box >= (e >= kLinLarge ? kLinMinBoxesLarge : kLinMinBoxes);
+  if (one_sided)
+    return e >= kLinMinElemsOne && e * n_box >= (e < 6000000 ? 20000000000ll : 6000000000ll) &&
+           n_box >= (e < 16000000 ? 512 : e < 30000000 ? 448 : e < 80000000 ? 256 : 128);
+  return e >= kLinMinElems && e * n_box >= (e < 6000000 ? 6000000000ll : 4000000000ll) &&
+         n_box >= (e < 16000000 ? 320 : e < 30000000 ? 240 : e < 80000000 ? 192 : 96);
 }
 
 int round_up(int x, int m) { return (x + m - 1) / m * m; }
@@ -514,10 +523,10 @@ void add_screen(const ibp::DevNet& d, const ibp::Tune& tune, int64_t n_box, ibp:
 
 // The linear sweep's arrays, in the memory of the base-flow partials (the
 // workspace does not grow); off where they do not fit.
-void add_linear(const ibp_network* net, int64_t n_box, ibp::WsLayout& lay) {
+void add_linear(const ibp_network* net, int64_t n_box, bool one_sided, ibp::WsLayout& lay) {
   const ibp::DevNet& d = net->dn;
   if (!d.lin_dig || !net->tune.k3_sparse || net->tune.k3_lin == 0) return;
-  if (net->tune.k3_lin < 0 && !linear_pays(d, n_box)) return;
+  if (net->tune.k3_lin < 0 && !linear_pays(d, n_box, one_sided)) return;
   const size_t B = (size_t)n_box, G = (B + ibp::kLinGroup - 1) / ibp::kLinGroup;
   size_t off = lay.part2;
   auto take = [&](size_t bytes) {
@@ -614,7 +623,7 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
   // one-sided calls with a screen keep it: few of their lines are swept (8192
   // boxes at 2000 buses: 2.2 ms for screen and sweep of the upper bounds, and the
   // linear sweep takes about 3)
-  if (lay.batched && !(one_sided && lay.fscreen)) add_linear(net, n_box, lay);
+  if (lay.batched && !(one_sided && lay.fscreen)) add_linear(net, n_box, one_sided, lay);
   if (flags & (IBP_F_CROWN | IBP_F_CROWN_REF)) {
     const ibp::DevNet& d = net->dn;
     const size_t B = (size_t)std::max<int64_t>(1, n_box);
