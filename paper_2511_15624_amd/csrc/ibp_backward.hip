@@ -274,8 +274,12 @@ __device__ __forceinline__ void k5b_step(const float4 (&x)[4], const float2 (&q)
 // about 2.7 us otherwise: 500 buses, 37 boxes 353 -> 63 us, 1024 boxes (1536 tiles of
 // boxes, lines and outage rows) 446 -> 329; 150 buses, 500 boxes 154 -> 35 us; 8316
 // buses, 4 boxes 423 -> 259 us.  With more tiles the chip is full and the plain form's
-// shared factor rows win: 500 buses, 2048 boxes (3072 tiles) 493 against 730 us.
-constexpr int64_t kK5SplitTiles = 1536;
+// shared factor rows win: 500 buses, 2048 boxes (3072 tiles) 493 against 730 us.  Short
+// outage rows leave the waves little to share, and their blocks' line sums are then the work:
+// at 19 outages 512 tiles 20 against 22 us, 1024 36 against 22; at 58 512 29 against
+// 49, 1024 53 against 50; at 118 1024 82 against 94, 1500 120 against 112; at 243 1500 204
+// against 222.
+inline int64_t k5_split_tiles(int K) { return std::min(1536, 460 + 5 * std::min(K, kK5ChunkTiled)); }
 
 template <int MODE, bool SPLIT>
 __global__ __launch_bounds__(SPLIT ? 512 : 256) void k5b_outage_vjp(DevNet net, void* ws, WsLayout lay, int64_t n_box,
@@ -1011,8 +1015,11 @@ __global__ __launch_bounds__(256) void k6m_ptdf_t_mfma(DevNet net, void* ws, WsL
 // 306 us; 2000 buses, 16 boxes 161 -> 38 us, 256 boxes 186 -> 87; 500 buses, 37 boxes
 // 40 -> 15), and fewer than eight 64-box tiles leave XCDs idle (8316 buses, 256 boxes
 // 3135 -> 1597 us).  From about 640 waves on the plain kernel's shared rows win: 500
-// buses, 2048 boxes (1024 waves) 45 against 51 us.
-constexpr int64_t kK6SplitWaves = 640;
+// buses, 2048 boxes (1024 waves) 45 against 51 us; with few chunks, which leave waves of the
+// block idle, from fewer on: at two chunks 256 waves 8.2 against 9.7 us, 376 13.9
+// against 9.9; at four 376 13.4 against 13.6, 564 17.6 against 13.8; at six 512 15.9
+// against 16.9.
+inline int64_t k6_split_waves(int Lp) { return std::min(640, 168 + 56 * (Lp / 32)); }
 
 __global__ __launch_bounds__(512) void k6m_ptdf_t_split(DevNet net, void* ws, WsLayout lay, int64_t n_box) {
   __shared__ double sh[8][8][64];
@@ -1125,7 +1132,7 @@ hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, co
   } else if (n_box >= kBatchMin && lay.batched && net.K > 0) {
     const int t = tm->start(7, s);
     const int64_t tiles = (n_box + kBT5 - 1) / kBT5;
-    const bool split = tiles * lay.k5_tiles * lay.k5_by <= kK5SplitTiles;
+    const bool split = tiles * lay.k5_tiles * lay.k5_by <= k5_split_tiles(net.K);
     const dim3 grid(lay.k5_tiles, lay.k5_by, (unsigned)(split ? tiles : (tiles + 3) / 4));
     const float2* cb_all = reinterpret_cast<const float2*>(static_cast<char*>(ws) + lay.cb);
     float2* cpart_all = reinterpret_cast<float2*>(static_cast<char*>(ws) + lay.cpart);
@@ -1163,7 +1170,7 @@ hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, co
     const int t = tm->start(8, s);
     if (lay.k2_mfma) {
       const int n_bt = (int)((n_box + kMB - 1) / kMB), n_nt = (net.Np + kMN - 1) / kMN;
-      if (n_bt <= 8 || (int64_t)n_bt * n_nt * 4 <= kK6SplitWaves)
+      if (n_bt <= 8 || (int64_t)n_bt * n_nt * 4 <= k6_split_waves(net.Lp))
         hipLaunchKernelGGL(k6m_ptdf_t_split, dim3(net.Np / 32, (unsigned)((n_box + 31) / 32)), dim3(512), 0, s, net, ws,
                            lay, n_box);
       else
