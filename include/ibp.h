@@ -382,10 +382,14 @@ ibp_status ibp_autotune(ibp_network* net, int64_t n_box, const float* box_lo, co
  * rule, else 1..8).  Results do not depend on them beyond float64 summation
  * order.  ibp_autotune_batched() times the candidates around the current
  * parameters on the caller's n_box >= 4 boxes (forward kernels on `stream`,
- * synchronizing; the base flows first, then the outage sweep with the chosen
- * base flows, then the same sweep over the lines the upper-penalty screen
- * marks, kept in the screen-upper setting below if faster) and keeps the
- * fastest; `chosen` (host int32[5], nullable) receives (k3_bt, k3_rows,
+ * synchronizing; the base flows first, then the outage sweep that two-sided
+ * calls of n_box boxes take with them, then the same sweep over the lines the
+ * upper-penalty screen marks, kept in the screen-upper setting below if
+ * faster) and keeps the fastest.  Where two-sided calls take the linear sweep,
+ * whose kernels these parameters do not reach, the outage sweep's parameters
+ * and the setting are chosen for calls with IBP_F_LOWER_ONLY.  On small networks it
+ * also times one block per box, and keeps it (k2_mfma = 1, k2_by <= 1, the
+ * screen-upper setting off) where that is faster.  `chosen` (host int32[5], nullable) receives (k3_bt, k3_rows,
  * k3_xcd, k2_mfma, k2_by).  The workspace must hold
  * ibp_workspace_bytes(net, n_box, IBP_F_AUTOTUNE).  ibp_get_tile() copies the
  * current parameters (host int32[7]: k2_nc, k3_kc, k3_bt, k3_rows, k3_xcd,

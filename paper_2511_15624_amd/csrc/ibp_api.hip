@@ -523,10 +523,10 @@ void add_screen(const ibp::DevNet& d, const ibp::Tune& tune, int64_t n_box, ibp:
 
 // The linear sweep's arrays, in the memory of the base-flow partials (the
 // workspace does not grow); off where they do not fit.
-void add_linear(const ibp_network* net, int64_t n_box, bool one_sided, ibp::WsLayout& lay) {
+void add_linear(const ibp_network* net, int64_t n_box, bool one_sided, const ibp::Tune& tune, ibp::WsLayout& lay) {
   const ibp::DevNet& d = net->dn;
-  if (!d.lin_dig || !net->tune.k3_sparse || net->tune.k3_lin == 0) return;
-  if (net->tune.k3_lin < 0 && !linear_pays(d, n_box, one_sided)) return;
+  if (!d.lin_dig || !tune.k3_sparse || tune.k3_lin == 0) return;
+  if (tune.k3_lin < 0 && !linear_pays(d, n_box, one_sided)) return;
   const size_t B = (size_t)n_box, G = (B + ibp::kLinGroup - 1) / ibp::kLinGroup;
   size_t off = lay.part2;
   auto take = [&](size_t bytes) {
@@ -552,22 +552,26 @@ void add_linear(const ibp_network* net, int64_t n_box, bool one_sided, ibp::WsLa
   lay = l;
 }
 
-ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
+// The layout, and with it the kernels, of a call with the tiles `tune`.
+ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags, const ibp::Tune& tune) {
   if (flags & IBP_F_AUTOTUNE) {
     // the largest layout over every tile pair (smallest tiles give most
     // partials), and from kBatchMin boxes on over every box-tiled candidate
-    ibp::Tune t = net->tune;
+    ibp::Tune t = tune;
     t.k2_nc = 32;
     t.k3_kc = 16;
     ibp::WsLayout big = layout_for(net, n_box, t, false);
     if (n_box >= ibp::kBatchMin) {
-      for (const ibp::Tune& f : flow_candidates(net, net->tune))
-        for (const ibp::Tune& c : sweep_candidates(net, n_box, f)) {
+      for (const ibp::Tune& f : flow_candidates(net, tune)) {
+        std::vector<ibp::Tune> tiles = sweep_candidates(net, n_box, f);
+        tiles.push_back(f);  // the present tiles serve where the dense sweep is not tuned
+        for (const ibp::Tune& c : tiles) {
           ibp::WsLayout l = layout_for(net, n_box, c, true);
           // and the upper-penalty screen, timed on the chosen tiles
           if (net->dn.K > 0) add_screen(net->dn, c, n_box, l);
           if (l.total > big.total) big = l;
         }
+      }
     }
     return big;
   }
@@ -576,11 +580,10 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
   // base flows add the buses in the order the float64 matrix products do, and the
   // outages pair as the box-tiled sweep's rows do, so that a line's or pair's float32
   // rounding is the same there.
-  const ibp::Tune& tune = net->tune;
   const bool micro = (flags & ~uint32_t(IBP_F_CROWN | IBP_F_CROWN_REF)) == 0 && batched && tune.micro &&
                      tune.k2b_mfma && tune.k2_by <= 1 && !tune.k3_scr && tune.k3_lin != 1 &&
                      ibp::micro_pays(net->dn, n_box);
-  ibp::WsLayout lay = layout_for(net, n_box, net->tune, batched && !micro);
+  ibp::WsLayout lay = layout_for(net, n_box, tune, batched && !micro);
   if (micro) {
     ibp::WsLayout tiled;
     ibp::plan_batched(net->dn, n_box, tiled, tune);
@@ -612,9 +615,9 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
   // the line screen of the one-sided sweeps (the backward's gradient of f_hi,
   // the forward's one-sided bounds) and of screened calls bounding f_lo
   const bool one_sided = (flags & (IBP_F_UPPER_ONLY | IBP_F_LOWER_ONLY)) != 0;
-  const bool scr_upper = (flags & IBP_F_SCREEN_UPPER) || (net->tune.k3_scr && !(flags & IBP_F_UPPER_ONLY));
+  const bool scr_upper = (flags & IBP_F_SCREEN_UPPER) || (tune.k3_scr && !(flags & IBP_F_UPPER_ONLY));
   if (lay.batched && net->dn.K > 0 && (one_sided || scr_upper || (flags & (IBP_F_BACKWARD | IBP_F_KEEP_PREP)))) {
-    add_screen(net->dn, net->tune, n_box, lay);
+    add_screen(net->dn, tune, n_box, lay);
     const bool side_ok = (flags & IBP_F_UPPER_ONLY) || scr_upper;
     lay.fscreen = side_ok && lay.fscreen;
   } else {
@@ -623,11 +626,11 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
   // one-sided calls with a screen keep it: few of their lines are swept (8192
   // boxes at 2000 buses: 2.2 ms for screen and sweep of the upper bounds, and the
   // linear sweep takes about 3)
-  if (lay.batched && !(one_sided && lay.fscreen)) add_linear(net, n_box, one_sided, lay);
+  if (lay.batched && !(one_sided && lay.fscreen)) add_linear(net, n_box, one_sided, tune, lay);
   if (flags & (IBP_F_CROWN | IBP_F_CROWN_REF)) {
     const ibp::DevNet& d = net->dn;
     const size_t B = (size_t)std::max<int64_t>(1, n_box);
-    ibp::plan_crown(d, n_box, lay, net->tune);
+    ibp::plan_crown(d, n_box, lay, tune);
     size_t off = lay.total;
     auto take = [&](size_t bytes) {
       const size_t o = off;
@@ -653,13 +656,13 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
     // launches: 2000 buses, 8 boxes 295 against 230 us, 64 boxes 471 against 583,
     // 1024 3.35 against 6.67 ms; 8316 buses, 4 boxes 1280 against 1234 us, 64 3.65
     // against 5.11 ms; 500 buses, 1024 boxes the same.
-    const bool pays = net->tune.k5_sparse && (int64_t)d.K * d.L * n_box >= 500000000;
+    const bool pays = tune.k5_sparse && (int64_t)d.K * d.L * n_box >= 500000000;
     if (lay.batched && d.K > 0 && pays && lay.k5s_tiles) {
       lay.rscreen = ibp::screen_fits(d, lay);
     } else if (lay.batched && d.K > 0 && pays) {
       ibp::WsLayout l = lay;
       l.total = 0;
-      add_screen(d, net->tune, n_box, l, lay.part2);
+      add_screen(d, tune, n_box, l, lay.part2);
       if (l.total <= lay.part2 + B * lay.k2_by * d.Lp * 2 * sizeof(double) && ibp::screen_fits(d, l)) {
         l.total = lay.total;
         l.fscreen = lay.fscreen;
@@ -669,6 +672,10 @@ ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
     }
   }
   return lay;
+}
+
+ibp::WsLayout layout(const ibp_network* net, int64_t n_box, uint32_t flags) {
+  return layout(net, n_box, flags, net->tune);
 }
 
 ibp::WsLayout layout_for(const ibp_network* net, int64_t n_box, const ibp::Tune& tune, bool batched = false) {
@@ -1219,15 +1226,17 @@ ibp_status ibp_autotune_batched(ibp_network* net, int64_t n_box, const float* bo
     if (!g.ok) return fail(IBP_E_DEVICE, "hipSetDevice failed");
     prep_forget(net, ws);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    const bool micro = ibp::micro_pays(net->dn, n_box);
     TuneScratch sc;
-    if (!sc.init(0)) return fail(IBP_E_DEVICE, "autotune events");
+    if (!sc.init(micro ? (size_t)n_box * 2 * sizeof(double) : 0)) return fail(IBP_E_DEVICE, "autotune events");
     const hipEvent_t e0 = sc.e0, e1 = sc.e1;
     ibp::KernelTimer off;
     ibp_status st = IBP_OK;
-    auto time_it = [&](auto launch) {
+    auto time_it = [&](auto launch, auto before) {
       float best = 1e30f;
       for (int rep = 0; rep < 3; ++rep) {  // the first run warms up
         float ms = 0.0f;
+        before();
         (void)hipEventRecord(e0, s);
         if (launch() != hipSuccess) st = fail(IBP_E_DEVICE, "autotune launch failed");
         (void)hipEventRecord(e1, s);
@@ -1237,52 +1246,105 @@ ibp_status ibp_autotune_batched(ibp_network* net, int64_t n_box, const float* bo
       }
       return best;
     };
+    auto nothing = [] {};
+    auto prepare = [&](const ibp::WsLayout& lay) {
+      if (ibp::launch_forward_prep(net->dn, n_box, box_lo, box_hi, ws, lay, s, &off) != hipSuccess)
+        st = fail(IBP_E_DEVICE, "autotune preparation failed");
+    };
+    // The box-tiled route of a call of both bounds (flags 0) or of f_lo alone.
+    auto route = [&](const ibp::Tune& t, uint32_t flags) {
+      ibp::Tune c = t;
+      c.micro = 0;
+      ibp::WsLayout lay = layout(net, n_box, flags, c);
+      lay.sides = flags ? 2 : 3;
+      return lay;
+    };
+    // the linear and screened sweeps: prepared each time (they use the base flows' memory)
+    auto sweep = [&](const ibp::WsLayout& lay) {
+      return time_it([&] { return ibp::launch_batched_sweeps(net->dn, n_box, ws, lay, s, &off, 1); },
+                     [&] { prepare(lay); });
+    };
     // base flows: box preparation once, then every engine / chunking (each
-    // writes only its own partials)
-    ibp::Tune best_t = net->tune;
-    {
+    // writes only its own partials); the fastest whose two-sided calls take the dense
+    // outage sweep and the fastest whose take the linear one (its arrays have to fit the
+    // partials)
+    struct Flows {
+      float ms = 1e30f;
+      ibp::Tune t;
+    } flows[2];
+    for (const ibp::Tune& c : flow_candidates(net, net->tune)) {
+      ibp::WsLayout lay = layout_for(net, n_box, c, true);
+      prepare(lay);
+      const float ms =
+          time_it([&] { return ibp::launch_batched_sweeps(net->dn, n_box, ws, lay, s, &off, 0); }, nothing);
+      Flows& f = flows[route(c, 0).lin];
+      if (st == IBP_OK && ms < f.ms) f = Flows{ms, c};
+    }
+    // The outage sweep of the calls with these flags: its tiles where it is the dense
+    // one, then the sweep over the lines the upper-penalty screen marks against it, where
+    // the setting would put the call there (it pays where few lines carry an active
+    // upper penalty: narrow boxes).  Returns the sweep's time.
+    auto tune_sweep = [&](ibp::Tune& t, uint32_t flags) {
+      t.k3_scr = 0;
+      const ibp::WsLayout now = route(t, flags);
       float best = 1e30f;
-      for (const ibp::Tune& c : flow_candidates(net, net->tune)) {
-        ibp::WsLayout lay = layout_for(net, n_box, c, true);
-        if (ibp::launch_forward_prep(net->dn, n_box, box_lo, box_hi, ws, lay, s, &off) != hipSuccess)
-          st = fail(IBP_E_DEVICE, "autotune preparation failed");
-        const float ms = time_it([&] { return ibp::launch_batched_sweeps(net->dn, n_box, ws, lay, s, &off, 0); });
+      if (now.lin) {
+        best = sweep(now);
+      } else {
+        prepare(now);
+        ibp::Tune pick = t;
+        for (const ibp::Tune& c : sweep_candidates(net, n_box, t)) {
+          const ibp::WsLayout lay = route(c, flags);
+          const float ms =
+              time_it([&] { return ibp::launch_batched_sweeps(net->dn, n_box, ws, lay, s, &off, 1); }, nothing);
+          if (st == IBP_OK && ms < best) {
+            best = ms;
+            pick = c;
+          }
+        }
+        t = pick;
+      }
+      ibp::Tune scr = t;
+      scr.k3_scr = 1;
+      const ibp::WsLayout lay = route(scr, flags);
+      if (lay.fscreen && !lay.lin) {
+        const float ms = sweep(lay);
         if (st == IBP_OK && ms < best) {
           best = ms;
-          best_t.k2b_mfma = c.k2b_mfma;
-          best_t.k2_by = c.k2_by;
+          t.k3_scr = 1;
         }
+      }
+      return best;
+    };
+    ibp::Tune best_t = flows[flows[1].ms < flows[0].ms].t;
+    if (st == IBP_OK && net->dn.K > 0) {
+      // the dense sweep only where its base flows are the faster ones
+      float ms = 1e30f;
+      if (flows[0].ms < flows[1].ms) ms = flows[0].ms + tune_sweep(best_t, 0);
+      if (st == IBP_OK && flows[1].ms < 1e30f && flows[1].ms + sweep(route(flows[1].t, 0)) < ms) {
+        // the tiles and the setting are then those of the calls for f_lo alone
+        best_t = flows[1].t;
+        tune_sweep(best_t, IBP_F_LOWER_ONLY);
       }
     }
-    // outage sweep: the chosen base flows prepared once, then every candidate
-    // (the line data sit before the per-call partials, at the same offsets)
-    if (st == IBP_OK && net->dn.K > 0) {
-      ibp::WsLayout prep = layout_for(net, n_box, best_t, true);
-      if (ibp::launch_forward_prep(net->dn, n_box, box_lo, box_hi, ws, prep, s, &off) != hipSuccess)
-        st = fail(IBP_E_DEVICE, "autotune preparation failed");
-      float best = 1e30f;
-      ibp::Tune pick = best_t;
-      for (const ibp::Tune& c : sweep_candidates(net, n_box, best_t)) {
-        ibp::WsLayout lay = layout_for(net, n_box, c, true);
-        const float ms = time_it([&] { return ibp::launch_batched_sweeps(net->dn, n_box, ws, lay, s, &off, 1); });
-        if (st == IBP_OK && ms < best) {
-          best = ms;
-          pick = c;
-        }
-      }
-      best_t = pick;
-      // the two-sided sweep over the lines the upper-penalty screen marks,
-      // against the dense one just picked (it pays where few lines carry an
-      // active upper penalty: narrow boxes)
-      ibp::Tune ts = best_t;
-      ts.k3_sparse = 1;
-      ibp::WsLayout lay = layout_for(net, n_box, ts, true);
-      add_screen(net->dn, ts, n_box, lay);
-      best_t.k3_scr = 0;
-      if (lay.fscreen) {
-        lay.sides = 3;
-        const float ms = time_it([&] { return ibp::launch_batched_sweeps(net->dn, n_box, ws, lay, s, &off, 1); });
-        if (st == IBP_OK && ms < best) best_t.k3_scr = 1;
+    // small networks: one block per box, if that beats the tiles found; calls take it with
+    // unsplit matrix-core base flows and no screen
+    if (st == IBP_OK && micro) {
+      ibp::Tune one = best_t;
+      one.k2b_mfma = 1;
+      one.k2_by = 1;
+      one.k3_scr = 0;
+      const ibp::WsLayout block = layout(net, n_box, 0, one);
+      if (!block.batched && layout(net, n_box, 0, best_t).batched) {
+        double* f = static_cast<double*>(sc.buf);
+        auto call = [&](const ibp::WsLayout& lay) {
+          return time_it(
+              [&] {
+                return ibp::launch_forward(net->dn, n_box, box_lo, box_hi, f, f + n_box, nullptr, ws, lay, s, &off);
+              },
+              nothing);
+        };
+        if (call(block) < call(route(best_t, 0)) && st == IBP_OK) best_t = one;
       }
     }
     if (st != IBP_OK) return st;
