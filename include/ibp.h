@@ -114,7 +114,12 @@ typedef struct ibp_network_info {
  * device = IBP_DEVICE_HOST_ONLY builds on the host only (no HIP call at all);
  * such a handle supports query/export/free but no compute call.
  * Synchronous.  On success *out owns host and device memory until
- * ibp_free_network.  Errors: INVALID_ARG, DISCONNECTED, ISLANDING_CTG,
+ * ibp_free_network.  The device holds two float32 copies of the outage factors
+ * (8 bytes per outage and line) and, from 2500000 of them on, the digit planes of
+ * the linear sweep of many boxes (10 bytes more; 8316 buses, 8000 outages: 1.1 GB
+ * beside 1.4).  Without the planes the dense sweep serves: with IBP_TILE
+ * "k3l=0" or "k3s=0", beyond 65280 lines, and where they would take over an eighth of
+ * the device's free memory.  Errors: INVALID_ARG, DISCONNECTED, ISLANDING_CTG,
  * ILL_CONDITIONED, OUT_OF_MEMORY, DEVICE. */
 ibp_status ibp_build_network(const ibp_network_desc* desc, int device, ibp_network** out);
 

@@ -312,15 +312,19 @@ ibp_status to_device(ibp_network* net, int device) {
     if ((st = upload(net, lt.data(), lt.size(), &d.lodfT)) != IBP_OK) return st;
     if ((st = upload(net, amax.data(), amax.size(), &d.lam_max)) != IBP_OK) return st;
     // digit planes of the linear sweep, made on the device from the uploaded
-    // factors; without them (no memory, a factor they cannot hold, or more lines
-    // than their sums hold) the dense sweep serves
+    // factors; without them (switched off, a factor they cannot hold, more lines than
+    // their sums hold, or over an eighth of the free memory, which the calls'
+    // workspaces need more) the dense sweep serves
     d.lin_dig = d.lin_dga = nullptr;
     const char* tile = std::getenv("IBP_TILE");
-    const bool wanted = (int64_t)h.K * h.L >= kLinMinElems || (h.K > 0 && tile && std::strstr(tile, "k3l=1"));
+    auto tile_is = [&](const char* setting) { return tile && std::strstr(tile, setting); };
+    const bool off = tile_is("k3l=0") || tile_is("k3s=0");
+    const bool wanted = !off && ((int64_t)h.K * h.L >= kLinMinElems || (h.K > 0 && tile_is("k3l=1")));
     if (wanted && h.L <= ibp::kLinMaxLines && *std::max_element(amax.begin(), amax.end()) < ibp::kLinMaxFactor) {
       void* p = nullptr;
       const size_t bytes = ibp::lin_digit_bytes(d), all = 2 * bytes + (size_t)d.Lp * 64 * sizeof(float);
-      if (hipMalloc(&p, all) == hipSuccess) {
+      size_t unused = 0, total = 0;
+      if (hipMemGetInfo(&unused, &total) == hipSuccess && all <= unused / 8 && hipMalloc(&p, all) == hipSuccess) {
         net->allocs.push_back(p);
         net->device_bytes += all;
         int8_t* dig = static_cast<int8_t*>(p);

@@ -1,6 +1,7 @@
 """Which calls of many boxes take the linear outage sweep: both bounds from fewer
 boxes on than the lower bound alone, whose dense sweep costs less, and neither
-below the sizes where the dense sweep is faster."""
+below the sizes where the dense sweep is faster.  And the device memory of handles
+that cannot take it."""
 import pytest
 
 from paper_2511_15624_amd import ibp, synth
@@ -21,3 +22,16 @@ def test_linear_sweep_by_size(n_bus, n_line, nb, both, lower):
     assert runs_linear(n, lambda: ibp.ibp_bound_boxes(n, lo, hi))[1] is both
     assert runs_linear(n, lambda: ibp.ibp_bound_boxes(n, lo, hi, flags=ibp.IBP_F_LOWER_ONLY))[1] is lower
     n.close()
+
+
+def test_no_digit_planes_where_the_sweep_is_off(monkeypatch):
+    net = synth.make_network(1300, 2000, 260, 650, 7)
+    held = {}
+    for tile in ("", "k3l=0", "k3s=0"):
+        monkeypatch.setenv("IBP_TILE", tile)
+        n = ibp.Network(net, device=0)
+        held[tile] = n.info.device_bytes
+        elements = n.n_ctg * n.n_line
+        n.close()
+    assert elements > 2500000
+    assert held["k3l=0"] == held["k3s=0"] <= held[""] - 10 * elements
