@@ -484,9 +484,14 @@ __device__ void finalize_box(const DevNet& net, void* ws, const std::conditional
   for (int f = 0; f < 12; ++f) x[f] = tot[f];
   double pad_hi = 0.0, pad_lo = 0.0;
   if constexpr (LIN) {
-    // what the linear sweep's float64 sums (absolute terms eh, el; their
-    // exceptions add at most twice those) and its 2^-38 factors may be off,
-    // beyond the part of the totals' float32 allowance that it does not use
+    // The allowance of the linear sweep's totals, u = kU32.  objective_interval scales
+    // them by 1 +- 4u.  Element roundings lie in the padded radii; of the sums,
+    // the parts added in float32 (bridges' quads and pairs near a kink two levels, heavy
+    // quads three) are off by at most 3u (1 + 2u) of themselves, and they are non-negative
+    // parts of totals of non-negative penalties.  So at least 0.99u of a total is left,
+    // and 0.5u of it pays here, as far as it goes, for what else may be off: the
+    // float64 sums (absolute terms eh, el, which also hold in full what the narrow boxes'
+    // correction moved; exceptions add at most twice those) and the 2^-38 factors.
     const double gF = (double)(net.L + net.K + 4096) * kU64;
     const float wm = __uint_as_float(
         *reinterpret_cast<const unsigned*>(ws_ptr<double>(ws, lay.box) + b * kBoxSlots + kWmax));

@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void kn_outages(DevNet net, void* ws, WsLayout
 // candidates bound it together: four waves per SIMD (128 registers) take 4.0 ms for
 // 18432 boxes at 2000 buses, three (134 registers) 5.0, five (spills) 5.2.
 constexpr float kHeavy = 4.0f;
-constexpr float kTinyRadius = 0x1p-6f;
+constexpr float kTinyRadius = 0x1p-5f;  // of the smallest limit
 constexpr int kList = 60;  // candidates of a line listed before they are evaluated
 constexpr int kNearRank = 4;  // of 64 sampled outages: the pair threshold is the 4th largest |Lam| w
 
@@ -376,8 +376,10 @@ __global__ __launch_bounds__(256, 4) void kn_lines(DevNet net, void* ws, WsLayou
     // In boxes of next to no width |Lam| r_k mostly lies below half a unit of h (of
     // g), and the dense sweep's float32 A (B) loses it: 3e-10 of the penalties at
     // 2000 buses, 1e-9 at 1000.  The same amount, estimated from the sampled
-    // outages, is left out here and charged to the float32 allowance.
-    if (__builtin_amdgcn_ballot_w64(in && rmax < kTinyRadius) != 0) {
+    // outages, is left out here.  The estimate need not be right: e holds, in full, what
+    // it moves the total by (the finalize multiplies e by the factor in `charge`).
+    const float tiny = kTinyRadius * (float)net.fmax_c_min;
+    if (__builtin_amdgcn_ballot_w64(in && rmax < tiny) != 0) {
       double uh[8] = {}, ul[8] = {};
       const float2* oq = ws_ptr<float2>(ws, lay.oc) + (size_t)g * net.K * kLinGroup + lane;
       const float* smp = net.lin_smp + (size_t)(l0 + w * 8) * 64;
@@ -390,7 +392,7 @@ __global__ __launch_bounds__(256, 4) void kn_lines(DevNet net, void* ws, WsLayou
           if (LO) ul[j] += (double)fmaf(-z, rk, fmaf(z, rk, q[j]) - q[j]);
         }
       }
-      const double per = rmax < kTinyRadius ? (double)net.K / 64.0 : 0.0;
+      const double per = rmax < tiny ? (double)net.K / 64.0 : 0.0;
       const double charge = 1.0 / (4.0 * (double)(net.L + net.K + 4096) * kU64);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
