@@ -287,7 +287,7 @@ VALU_PEAK_SOURCE = ("MI355X float32 vector peak 157.3 TFLOP/s with an FMA counte
                     "cycle, above what 16 lanes per clock allow (profiles/ibp_batched_counters_c2000.md), and "
                     "the FMA probe's measured rate is reported beside it (alu_probe)")
 I8_OPS_PER_EVAL = 40  # int8 operations per box-outage-line evaluation of the linear sweep's products
-MFMA_I8_PEAK = 5.0e15  # dense int8 matrix operations/s
+MFMA_I8_PEAK = 5.0e15  # dense int8 matrix operations/s (nominal: 2 x bf16's 2.5e15, a multiply-add counted as two)
 # VALU ops per element of the chord-relaxation sweep: post-outage centre and
 # the two interval ends (5), the clipped lower end (3), the slope and its
 # quantisation (8), the intercept and its padding (4), the value bound (6),

@@ -166,10 +166,13 @@ void ibp_free_network(ibp_network* net);
  * active lower penalty either) and the sweep sums both sides, or the upper
  * side alone, over the marked lines.  That pays where few lines carry an
  * active upper penalty (the centre points of sub-boxes: 12.3 -> 7.2 ms at
- * 8192 points) and costs more than it saves on wide sub-boxes.  Two-sided calls
- * of many boxes take the linear sweep with the flag or without it (its bounds
- * are within 1e-9 of the dense sweep's; IBP_TILE=k3l=0 keeps that).  At most
- * one of the two side flags;
+ * 8192 points) and costs more than it saves on wide sub-boxes.  Calls of many
+ * boxes on networks of 2500000 outage elements or more take the linear sweep
+ * instead: two-sided ones with the screen's flag or without it, IBP_F_LOWER_ONLY ones
+ * without it and from more boxes on.  Its bounds are certified like the dense
+ * sweep's and differ from them by float32 roundings (measured, not promised:
+ * 1.3e-9 at most on the synthetic networks, 2.6e-6 where every line's limit lies on
+ * its flow; IBP_TILE=k3l=0 keeps the dense sweep).  At most one of the two side flags;
  * IBP_F_SCREEN_UPPER not with IBP_F_UPPER_ONLY. */
 #define IBP_F_UPPER_ONLY 32u
 #define IBP_F_LOWER_ONLY 64u
@@ -372,7 +375,9 @@ ibp_status ibp_kernel_times(ibp_network* net, int32_t n_ids, double* total_ms, i
  * float64 matrix cores (the default; both sum the same products); "ckb=2"
  * or "ckb=4" makes the box-tiled chord-relaxation sweep of
  * ibp_crown_lower_boxes keep two or four boxes per lane instead of one (same
- * results). */
+ * results); "k3l=0" keeps calls of many boxes from the linear outage sweep and
+ * "k3l=1" makes them take it wherever its arrays fit; "mb=0" keeps two-sided calls of
+ * several boxes on small networks box-tiled (default: one block per box). */
 #define IBP_F_AUTOTUNE 2u /* workspace query only: size for every tile pair */
 ibp_status ibp_set_tile(ibp_network* net, int32_t k2_nc, int32_t k3_kc);
 ibp_status ibp_autotune(ibp_network* net, int64_t n_box, const float* box_lo, const float* box_hi,

@@ -1053,7 +1053,8 @@ __global__ __launch_bounds__(256, MINB) void kc1c_chord(DevNet net, void* ws, Ws
 // and box, a lane each, wait in LDS until sixteen such rows are added up together (a
 // reduction of its own per line took half of the sweep's instructions).
 //
-// 1024 sub-boxes at 2000 buses 9.6 -> 3.9 ms, 64 at 8316 buses 6.9 -> 2.7 ms; one box
+// 1024 sub-boxes at 2000 buses 9.6 -> 3.5 to 4.2 ms (by the boxes), 64 at 8316 buses
+// 6.9 -> 2.7 ms; one box
 // per wave 4.6 ms (factors read twice), four 6.2 (two waves per SIMD).  Below about 2048
 // waves the per-line sweep's smaller units fill the chip better: 64 boxes at 500 buses
 // (352 waves) 63 against 163 us, 16 at 2000 buses (1600 waves) the same.

@@ -195,8 +195,9 @@ __global__ __launch_bounds__(256) void kn_outages(DevNet net, void* ws, WsLayout
 //    the lower side (KN2h).  Their float32 units are the coarsest, so that almost
 //    all of the difference between this sweep and the dense one (which rounds its
 //    elements and sums) comes from a few of them; swept like there, both sweeps'
-//    bounds agree to 1e-9 (65 networks of 1000 to 8300 buses, sub-boxes, periods and
-//    whole boxes).  18432 boxes at 2000 buses: 3.1 ms (kHeavy = 3: 4.7, 2: 9.9).
+//    bounds agreed to 1e-9 (measured, not assured: 65 networks of 1000 to 8300 buses,
+//    sub-boxes, periods and whole boxes; points of zero width at 1500 buses 1.3e-9; every
+//    line's limit on its flow 2.6e-6 of a small bound).  18432 boxes at 2000 buses: 3.1 ms (kHeavy = 3: 4.7, 2: 9.9).
 // Blocks of one group of boxes run on one XCD, whose L2 then holds the group's
 // (c_k, r_k) (1.5 MB at 2954 outages).  Loads and the float64 evaluations of the
 // candidates bound it together: four waves per SIMD (128 registers) take 4.0 ms for
@@ -684,7 +685,7 @@ __global__ __launch_bounds__(256) void kn_heavy(DevNet net, void* ws, WsLayout l
       }
     }
     for (; k < k1; k += 2) {
-      // an odd last outage is paired with itself at zero factors and r = NaN: no penalty
+      // an odd last outage is paired with itself at r = NaN, whose penalties are 0
       const bool on = k + 1 < k1;
       const int kb = on ? k + 1 : k;
       const float2 oa = oc[(size_t)k * kLinGroup];
