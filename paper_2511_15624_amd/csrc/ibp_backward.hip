@@ -1110,7 +1110,7 @@ void plan_backward(const DevNet& net, WsLayout& lay) {
   const int lp4 = net.Lp / 4;
   lay.k5_tiles = (lp4 + 63) / 64;
   lay.k5_chunk = lay.batched ? kK5ChunkTiled : kK5Chunk;
-  lay.k5_by = std::max(1, (net.K + lay.k5_chunk - 1) / lay.k5_chunk);
+  lay.k5_by = (net.K + lay.k5_chunk - 1) / lay.k5_chunk;  // (none without outages: nothing writes their partials)
 }
 
 hipError_t launch_backward_sweeps(const DevNet& net, int64_t n_box, void* ws, const WsLayout& lay,
